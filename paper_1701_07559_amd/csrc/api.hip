@@ -107,8 +107,18 @@ void* pinned(mdwf_ctx* c, size_t n, mdwf_status* st) {
 }
 
 // K5 = (4 - M5) B + 1 - C = a + b C.  Its inverse on each chirality, using
-// C^L5 = -m_q: K5^-1 = [a (1 + m_q z^L5)]^-1 sum_{k<L5} z^k C^k, z = -b/a;
-// B K5^-1 is the product of the two polynomials reduced with C^L5 = -m_q.
+// C^L5 = -m_q: K5^-1 = [a (1 + m_q z^L5)]^-1 sum_{k<L5} z^k C^k, z = -b/a.
+// A product (p + q C)(1 - z C)^-1 as the recurrence of five_lanes: the terms
+// A v + B e with A = p, B = q + p z, and the wall factor w.
+static void set_rec(double r[4], double p, double q, double z, double mq, int L5) {
+    double zl = 1.0;
+    for (int k = 0; k < L5; ++k) zl *= z;
+    r[0] = p;
+    r[1] = q + p * z;
+    r[2] = z;
+    r[3] = -mq / (1.0 + mq * zl);
+}
+
 RhsCoef make_coef(const mdwf_action& a, double mq) {
     RhsCoef c;
     std::memset(&c, 0, sizeof(c));
@@ -127,10 +137,7 @@ RhsCoef make_coef(const mdwf_action& a, double mq) {
         c.kinv[k] = zk * norm;
         zk *= z;
     }
-    c.m[0] = a.b5 * c.kinv[0] - mq * a.c5 * c.kinv[L5 - 1];
-    for (int k = 1; k < L5; ++k) c.m[k] = a.b5 * c.kinv[k] + a.c5 * c.kinv[k - 1];
-    // B = b5 + c5 C has the same closed-form inverse with (a, b) -> (b5, c5);
-    // K5 B^-1 is again reduced with C^L5 = -m_q
+    // B = b5 + c5 C has the same closed-form inverse with (a, b) -> (b5, c5)
     const double zb = -a.c5 / a.b5;
     double zbl = 1.0;
     for (int k = 0; k < L5; ++k) zbl *= zb;
@@ -140,14 +147,14 @@ RhsCoef make_coef(const mdwf_action& a, double mq) {
         c.binv[k] = zbk * nb;
         zbk *= zb;
     }
-    c.w[0] = ka * c.binv[0] - mq * kb * c.binv[L5 - 1];
-    for (int k = 1; k < L5; ++k) c.w[k] = ka * c.binv[k] + kb * c.binv[k - 1];
+    set_rec(c.rm, a.b5 / ka, a.c5 / ka, z, mq, L5);   // K5^-1 = (1 - z C)^-1 / ka
+    set_rec(c.rw, ka / a.b5, kb / a.b5, zb, mq, L5);  // B^-1 = (1 - zb C)^-1 / b5
     return c;
 }
 
 // Table of the second kernel of the symmetric Schur form (Sec. VII names
 // both even-odd forms) K5^-1 S = 1 - 1/4 K5^-1 D_eo (B K5^-1) D_oe B: its
-// dense epilogue is K5^-1 (m = kinv) and its centre term the identity
+// epilogue is K5^-1 (rm) and its centre term the identity
 // (k5 = 1 + 0 C).  K5^-1 does not commute with the hop (C carries the chiral
 // projectors, the hop's 1 -+ gamma_mu flips chirality), so it is applied
 // after the hop, in kernel B; the adjoint S^+ K5^-+ applies K5^-+ to the
@@ -155,7 +162,7 @@ RhsCoef make_coef(const mdwf_action& a, double mq) {
 // the untransformed input.
 RhsCoef make_coef_sym(const mdwf_action& a, double mq) {
     RhsCoef c = make_coef(a, mq);
-    for (int k = 0; k < kMaxL5; ++k) c.m[k] = c.kinv[k];
+    set_rec(c.rm, 1.0 / c.k5[0], 0.0, -c.k5[1] / c.k5[0], mq, a.L5);
     c.k5[0] = 1.0;
     c.k5[1] = 0.0;
     return c;
@@ -432,10 +439,12 @@ mdwf_status mdwf_create(const mdwf_geometry* geom, int hip_device, void* hip_str
     g.fY = FastDiv(uint32_t(g.Y));
     g.fZ = FastDiv(uint32_t(g.Z));
     // default launch shape (mdwf_autotune refines it per precision): z-blocks
-    // of 4 (or 2) planes with t inside; the MDWF_TILE ("bx,by,bz,bt"),
-    // MDWF_XCD_REMAP, MDWF_NT_STORE, MDWF_LINK_MODE and MDWF_RHS_GROUP
-    // variables override it
-    mdwf_launch_tune t0{{g.Xh, g.Y, (g.Z % 4 == 0) ? 4 : 2, 1}, 1, 0, 0, 0, 0.0, 0};
+    // of 4 (or 2) planes with t inside; links staged in LDS (L5 >= 8; against
+    // every lane loading them: FP32 hop 316 -> 277 us and FP64 S 1383 -> 1284 us
+    // at 24^3 x 64, L5 = 8, and no shape measured slower).  The MDWF_TILE
+    // ("bx,by,bz,bt"), MDWF_XCD_REMAP, MDWF_NT_STORE, MDWF_LINK_MODE and
+    // MDWF_RHS_GROUP variables override it
+    mdwf_launch_tune t0{{g.Xh, g.Y, (g.Z % 4 == 0) ? 4 : 2, 1}, 1, 0, 1, 0, 0.0, 0};
     if (const char* e = std::getenv("MDWF_TILE")) {
         int b[4];
         if (std::sscanf(e, "%d,%d,%d,%d", &b[0], &b[1], &b[2], &b[3]) == 4 && tile_fits(g, b))

@@ -5,24 +5,23 @@
 // one wavefront (64 / L5 sites per wave; the remaining lanes idle).  All lanes
 // of a site read the same eight links, so a link is fetched once per site and
 // reused across the fifth dimension, and the fifth-dimension couplings (B, C,
-// K5 and the dense B K5^-1) become exchanges inside that lane group:
-// ds_bpermute for the nearest-slice terms, an LDS tile for the dense L5 x L5
-// polynomials.  Spinors are read 16 bytes per lane from the structure-of-
-// arrays layout, so a wave's loads of one block are contiguous.
+// K5 and B K5^-1) become exchanges inside that lane group:
+// ds_bpermute for the nearest-slice terms, a recurrence through an LDS tile for
+// the inverses (five_lanes).  Spinors are read 16 bytes per lane from the
+// structure-of-arrays layout, so a wave's loads of one block are contiguous.
 #include "hop_device.h"
 
 namespace mdwf {
 
-// Waves per SIMD the hop kernels are compiled for: kernels B / B^+ of the
-// right-preconditioned FP16 CG operator fit six waves (80 VGPRs, no spills)
-// with the table-driven centre term; the others take what their registers
-// allow (held to six, kernels A / A^+ would spill).
-template <Prec P, int K> constexpr int hop_waves_per_eu() {
-    return (P == P16 && (K == HOP_SCHUR_B_RP || K == HOP_SCHUR_B_DAG_RP)) ? 6 : 1;
-}
+// Waves per SIMD the hop kernels are compiled for.  FP16: five (96 VGPRs, no
+// spills); left free, the scheduler takes 130 registers for kernels A / A^+
+// with staged links and they run 20 % slower, at six kernel B of S spills.
+// FP32 and FP64 take what their loads in flight need: held to four and three
+// waves they spill and run 18 % and 7 % slower.
+template <Prec P, int LM> constexpr int hop_waves_per_eu() { return (P == P16 && LM != 3) ? 5 : 1; }
 
 template <Prec P, int K, int LM>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop_waves_per_eu<P, K>()))) k_hop(const Geo g, const HopDev a) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop_waves_per_eu<P, LM>()))) k_hop(const Geo g, const HopDev a) {
     using R = typename Real<P>::T;
     using TR = HopTraits<K>;
     const int L5 = g.L5;
@@ -79,11 +78,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     nb.fp1 = (s == L5 - 1) ? -mq : R(1);
 
     const void* in = at_rhs(a.in, a.stride, rhs);
-    // -0 is an exact additive identity, so the first direction's sums into
-    // res compile to plain moves (+0 would need its own register clears)
     cx<R> res[12];
-#pragma unroll
-    for (int c = 0; c < 12; ++c) res[c] = {R(-0.0), R(-0.0)};
 
     // neighbours of the output site (used only by valid lanes)
     const int x = 2 * xh + ((y + z + t + a.out_parity) & 1);
@@ -114,49 +109,16 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
                             uint32_t(n_ym * L5 + s), uint32_t(n_zp * L5 + s), uint32_t(n_zm * L5 + s),
                             uint32_t(n_tp * L5 + s), uint32_t(n_tm * L5 + s)};
 
-    // LDS: link stage (when a wave holds at most kStageSites sites) and, for
-    // kernels A / A^+, the epilogue tile, which reuses the same bytes
-    constexpr int NP = LinkStage<P>::NP;
-    constexpr int kDirBytes = kStageSites * NP * 16;
-    constexpr int kLinkBytes = LM == 1 ? kWaves * 8 * kDirBytes : 0;
-    // the dense polynomials' tile: all twelve components for the epilogue of
-    // kernels A / A^+, six (two passes) for the centre term of B / B^+
-    constexpr int kEpiBytes = (TR::epi == 1 || TR::epi == 2) ? 12 * kBlock * int(sizeof(cx<R>))
-                            : (TR::cen == 4 || TR::cen == 5) ? 6 * kBlock * int(sizeof(cx<R>)) : 0;
-    constexpr int kSmem = kLinkBytes > kEpiBytes ? kLinkBytes : kEpiBytes;
-    __shared__ __align__(16) unsigned char smem[kSmem > 0 ? kSmem : 16];
-    // Dense centre term sum_k w_k C^k (or its adjoint) of kernels B / B^+:
-    // the workgroup's RHS gets a table (dynamic LDS, L5 x L5 entries) of the
-    // coefficient each lane applies to each source slice, dtab[s][j] = (P+
-    // coefficient, P- coefficient) with the -m_q of the wrap folded in, so
-    // the sums run over source slices with no index arithmetic.  C^k moves
-    // the P+ spins up (slice s reads s - k) and the P- spins down (s reads
-    // s + k); the adjoint swaps the two.  (The same table in the epilogue of
-    // kernels A / A^+ cost them occupancy and made them slower.)
-    constexpr bool kDense = dense_centre<K>();
-    constexpr bool kDenseAdj = TR::cen == 5;
-    extern __shared__ __align__(16) unsigned char hop_dyn_lds[];
-    cx<R>* const dtab = reinterpret_cast<cx<R>*>(hop_dyn_lds);
-    if constexpr (kDense) {
-        const double* poly = cf.w;
-        for (int e = tid; e < L5 * L5; e += kBlock) {
-            const int ss = e / L5, j = e - ss * L5;
-            const R dn = (j <= ss) ? R(poly[ss - j]) : -mq * R(poly[ss - j + L5]);   // read j = s - k
-            const R up = (j >= ss) ? R(poly[j - ss]) : -mq * R(poly[j - ss + L5]);   // read j = s + k
-            dtab[e] = kDenseAdj ? cx<R>{up, dn} : cx<R>{dn, up};
-        }
-    }
-    unsigned char* lslot = smem + size_t(wave) * 8 * kDirBytes + size_t(sw) * NP * 16;
+    // LDS, per wave: the staged links and, once the hop is done, the tile of
+    // five_lanes in the same bytes
+    constexpr int kLinkBytes = LM == 1 ? stage_bytes<P>() : 0;
+    constexpr bool kFive = TR::epi == 1 || TR::epi == 2 || TR::cen == 4 || TR::cen == 5;
+    constexpr int kFiveBytes = kFive ? (five_bytes<R>() + 15) / 16 * 16 : 0;
+    constexpr int kSmem = kLinkBytes > kFiveBytes ? kLinkBytes : kFiveBytes;
+    __shared__ __align__(16) unsigned char smem[kWaves][kSmem > 0 ? kSmem : 16];
+    unsigned char* const lw = smem[wave];
+    cx<R>* const ftile = reinterpret_cast<cx<R>*>(lw);
     const int a0 = gbase << 2;
-    if constexpr (LM == 1) {
-        if (valid) {
-            for (int b = s; b < NP; b += L5)
-#pragma unroll
-                for (int d = 0; d < 8; ++d)
-                    LinkStage<P>::copy_part(seg[d], lblk, lidx[d], b, lslot + d * kDirBytes + b * 16);
-        }
-        __syncthreads();
-    }
 
     if constexpr (LM == 3) {
         // FP16 on the matrix cores: lane s of the site group holds row s & 3
@@ -201,12 +163,26 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
 #pragma unroll
             for (int c = 0; c < 3; ++c) res[sp * 3 + c] = {S * acc[2 * sp][c], S * acc[2 * sp + 1][c]};
     } else if (valid) {
+        // LM == 1: this lane's direction of the links
+        LinkStage<P> stg;
+        if constexpr (LM == 1) {
+            const int d = s & 7, mu = d >> 1;
+            const uint32_t nm = uint32_t(mu == 0 ? n_xm : mu == 1 ? n_ym : mu == 2 ? n_zm : n_tm);
+            if (s < 8) stg.load(((d & 1) ? lk : lo) + mu * ls, lblk, (d & 1) ? nm : ui);
+        }
+        auto stage = [&]() {
+            if constexpr (LM == 1) {
+                if (s < 8) stg.put(lw, s, sw);
+                wave_sync();
+            }
+        };
         if constexpr (P == P64) {
             // FP64: one direction in flight (two would exceed the register file)
             Raw<P> r;
+            stage();
 #define MDWF_DIR(d)                                                                 \
     r.load(seg[d], lidx[d], lblk, src, jn[d], sblk, LM == 0);                      \
-    dir_term<P, D, PB, d, LM>(res, r, lslot + (d) * kDirBytes, a0, nb, b5, c5);
+    dir_term<P, D, PB, d, LM>(res, r, lw, sw, a0, nb, b5, c5);
             MDWF_DIR(0) MDWF_DIR(1) MDWF_DIR(2) MDWF_DIR(3) MDWF_DIR(4) MDWF_DIR(5) MDWF_DIR(6) MDWF_DIR(7)
 #undef MDWF_DIR
         } else {
@@ -214,51 +190,22 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
             Raw<P> r0, r1;
             r0.load(seg[0], lidx[0], lblk, src, jn[0], sblk, LM == 0);
             if constexpr (LM == 2) r0.load_part(seg[0], lidx[0], lblk, s);
+            stage();
 #define MDWF_STEP(d, rc, rn)                                                          \
     rn.load(seg[(d) + 1], lidx[(d) + 1], lblk, src, jn[(d) + 1], sblk, LM == 0);     \
     if constexpr (LM == 2) rn.load_part(seg[(d) + 1], lidx[(d) + 1], lblk, s);        \
-    dir_term<P, D, PB, d, LM>(res, rc, lslot + (d) * kDirBytes, a0, nb, b5, c5);
+    dir_term<P, D, PB, d, LM>(res, rc, lw, sw, a0, nb, b5, c5);
             MDWF_STEP(0, r0, r1) MDWF_STEP(1, r1, r0) MDWF_STEP(2, r0, r1) MDWF_STEP(3, r1, r0)
             MDWF_STEP(4, r0, r1) MDWF_STEP(5, r1, r0) MDWF_STEP(6, r0, r1)
 #undef MDWF_STEP
-            dir_term<P, D, PB, 7, LM>(res, r1, lslot + 7 * kDirBytes, a0, nb, b5, c5);
+            dir_term<P, D, PB, 7, LM>(res, r1, lw, sw, a0, nb, b5, c5);
         }
     }
 
     // ---- epilogue on the hop result
     if constexpr (TR::epi == 1 || TR::epi == 2) {
-        // dense B K5^-1 = sum_k m_k C^k (or its adjoint) across the L5 lanes;
-        // the tile reuses the link stage once every wave is past its hop
-        cx<R>* sh = reinterpret_cast<cx<R>*>(smem);
-        if constexpr (LM == 1) __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 12; ++c) sh[c * kBlock + tid] = res[c];
-        __syncthreads();
-        if (valid) {
-            const int tbase = tid - s;
-            // k = 0 (C^0 = 1) starts the sums
-            cx<R> o[12];
-            const R m0 = R(cf.m[0]);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) o[c] = m0 * sh[c * kBlock + tid];
-            for (int k = 1; k < L5; ++k) {
-                const R mk = R(cf.m[k]);
-                // C^k on P+ reads slice s-k, on P- slice s+k (adjoint: swapped)
-                int su = (TR::epi == 1) ? s - k : s + k;
-                int sd = (TR::epi == 1) ? s + k : s - k;
-                R fu = mk, fd = mk;
-                if (su < 0) { su += L5; fu = -mq * mk; }
-                if (su >= L5) { su -= L5; fu = -mq * mk; }
-                if (sd < 0) { sd += L5; fd = -mq * mk; }
-                if (sd >= L5) { sd -= L5; fd = -mq * mk; }
-#pragma unroll
-                for (int c = 0; c < 6; ++c) o[c] = o[c] + fu * sh[c * kBlock + tbase + su];
-#pragma unroll
-                for (int c = 6; c < 12; ++c) o[c] = o[c] + fd * sh[c * kBlock + tbase + sd];
-            }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) res[c] = o[c];
-        }
+        // B K5^-1 (or its adjoint) across the L5 lanes
+        five_lanes<TR::epi == 2>(res, ftile, cf.rm, lane, L5, spw);
     } else if constexpr (TR::epi == 3) {
         if (valid) {   // B^+ = b5 + c5 C^+
             cx<R> cr[12];
@@ -268,15 +215,12 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
         }
     }
 
-    // dense centre term sum_k w_k C^k (or its adjoint) on the centre field:
-    // the L5 lanes of a site exchange their values through LDS
+    // K5 B^-1 (or its adjoint) on the centre field
     cx<R> cd[12];
     if constexpr (TR::cen == 4 || TR::cen == 5) {
-        cx<R> cv[12];
         // lanes past the lattice load site 0 (in bounds; no valid lane reads them)
-        Field<P>::load(at_rhs(a.centre, a.stride, rhs), g.Vh, valid ? i * L5 + s : 0, cv);
-        if constexpr (LM == 1) __syncthreads();   // every wave is past the link stage
-        dense_poly_lanes(cv, cd, reinterpret_cast<cx<R>*>(smem), dtab + s * L5, tid, s, L5, valid);
+        Field<P>::load(at_rhs(a.centre, a.stride, rhs), g.Vh, valid ? i * L5 + s : 0, cd);
+        five_lanes<TR::cen == 5>(cd, ftile, cf.rw, lane, L5, spw);
     }
 
     double n2 = 0.0;
@@ -303,13 +247,19 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
 #pragma unroll
             for (int c = 0; c < 12; ++c) res[c] = hc * res[c];
         }
-        if (g.nt_store[P]) Field<P>::template store<true>(at_rhs(a.out, a.stride, rhs), g.Vh, j, res);
-        else Field<P>::store(at_rhs(a.out, a.stride, rhs), g.Vh, j, res);
-        if (TR::norm && a.partials) {
-            R acc = R(0);
+        void* out = at_rhs(a.out, a.stride, rhs);
+        if constexpr (TR::norm && P == P16) {   // the norm from the stored halves
+            n2 = g.nt_store[P] ? Field<P>::template store_norm2<true>(out, g.Vh, j, res)
+                               : Field<P>::template store_norm2<false>(out, g.Vh, j, res);
+        } else {
+            if (g.nt_store[P]) Field<P>::template store<true>(out, g.Vh, j, res);
+            else Field<P>::store(out, g.Vh, j, res);
+            if (TR::norm && a.partials) {
+                R acc = R(0);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) acc += res[c].re * res[c].re + res[c].im * res[c].im;
-            n2 = double(acc);
+                for (int c = 0; c < 12; ++c) acc += res[c].re * res[c].re + res[c].im * res[c].im;
+                n2 = double(acc);
+            }
         }
     }
     if (TR::norm && a.partials) {
@@ -361,17 +311,15 @@ static void launch_hop_t(const Geo& g, const GaugeSet& gs, HopLaunch& L, hipStre
     a.partials = L.partials;
     L.nblocks_per_rhs = a.nblk;
     dim3 grid(a.nblk * L.nrhs);
-    // the dense polynomial's coefficient table (see k_hop)
-    const size_t dyn = dense_centre<K>() ? size_t(g.L5) * g.L5 * sizeof(cx<typename Real<P>::T>) : 0;
     if (lm == 1) {
-        hipLaunchKernelGGL((k_hop<P, K, 1>), grid, dim3(kBlock), dyn, st, g, a);
+        hipLaunchKernelGGL((k_hop<P, K, 1>), grid, dim3(kBlock), 0, st, g, a);
     } else if (lm == 2) {
-        if constexpr (P != P64) hipLaunchKernelGGL((k_hop<P, K, 2>), grid, dim3(kBlock), dyn, st, g, a);
+        if constexpr (P != P64) hipLaunchKernelGGL((k_hop<P, K, 2>), grid, dim3(kBlock), 0, st, g, a);
     } else if (lm == 3) {
         if constexpr (P == P16 && !HopTraits<K>::preB)
-            hipLaunchKernelGGL((k_hop<P, K, 3>), grid, dim3(kBlock), dyn, st, g, a);
+            hipLaunchKernelGGL((k_hop<P, K, 3>), grid, dim3(kBlock), 0, st, g, a);
     } else {
-        hipLaunchKernelGGL((k_hop<P, K, 0>), grid, dim3(kBlock), dyn, st, g, a);
+        hipLaunchKernelGGL((k_hop<P, K, 0>), grid, dim3(kBlock), 0, st, g, a);
     }
 }
 

@@ -173,7 +173,7 @@ __device__ __forceinline__ void plane_term(cx<typename Real<P>::T> acc[12], cons
         su3_mul_h<(DIR > 0)>(U, z1, z2, w);
 #pragma unroll
         for (int c = 0; c < 6; ++c) w[c] = nrm * w[c];
-        reconstruct_add<MU>(float(sg), w, acc);
+        reconstruct_add<MU, false>(float(sg), w, acc);
     } else {
         using R = typename Real<P>::T;
         cx<R> psi[12], U[9];
@@ -183,7 +183,7 @@ __device__ __forceinline__ void plane_term(cx<typename Real<P>::T> acc[12], cons
         cx<R> h[6], w[6];
         project<MU>(sg, psi, h);
         su3_mul<(DIR > 0)>(U, h, w);
-        reconstruct_add<MU>(sg, w, acc);
+        reconstruct_add<MU, false>(sg, w, acc);
     }
 }
 
@@ -410,7 +410,7 @@ __device__ __forceinline__ void rb_term(cx<float> acc[12], const cx<float> psi[1
     cx<float> h[6], w[6];
     project<MU>(sg, psi, h);
     su3_mul<(DIR > 0)>(U, h, w);
-    reconstruct_add<MU>(sg, w, acc);
+    reconstruct_add<MU, false>(sg, w, acc);
 }
 
 template <int K>

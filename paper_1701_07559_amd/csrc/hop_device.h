@@ -68,11 +68,19 @@ __device__ __forceinline__ void project(R sg, const cx<R> in[12], cx<R> h[6]) {
     }
 }
 
-template <int MU, typename R>
+// FIRST: acc is set instead of added to
+template <int MU, bool FIRST, typename R>
 __device__ __forceinline__ void reconstruct_add(R sg, const cx<R> w[6], cx<R> acc[12]) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const cx<R> w0 = w[a], w1 = w[3 + a];
+        if (FIRST) {
+            acc[a] = w0;
+            acc[3 + a] = w1;
+            acc[6 + a] = -sg * (MU == 0 ? timesI(w1) : MU == 1 ? w1 : MU == 2 ? timesI(w0) : w0);
+            acc[9 + a] = (MU == 1 || MU == 2 ? sg : -sg) * (MU == 0 ? timesI(w0) : MU == 1 ? w0 : MU == 2 ? timesI(w1) : w1);
+            continue;
+        }
         acc[a] = acc[a] + w0;
         acc[3 + a] = acc[3 + a] + w1;
         if (MU == 0) {        // -sg G^+ w = (-sg i w1, -sg i w0)
@@ -211,13 +219,13 @@ template <int K> struct HopTraits {
     static constexpr bool dag = (K == HOP_D5_DAG || K == HOP_SCHUR_A_DAG || K == HOP_SCHUR_B_DAG || K == HOP_BARE_DAG ||
                                  K == HOP_SCHUR_B_DAG_RP);
     static constexpr bool preB = (K == HOP_D5 || K == HOP_SCHUR_A || K == HOP_PREP);
-    // epilogue on the hop result: 0 none, 1 sum_k m_k C^k (B K5^-1, or K5^-1
-    // for the symmetric form's kernel B), 2 its adjoint, 3 B^+
+    // epilogue on the hop result: 0 none, 1 B K5^-1 (K5^-1 in the
+    // symmetric form's kernel B), 2 its adjoint, 3 B^+
     static constexpr int epi = (K == HOP_SCHUR_A || K == HOP_SCHUR_B_SYM || K == HOP_SCHUR_A_RP) ? 1
                              : (K == HOP_SCHUR_A_DAG) ? 2
                              : (K == HOP_D5_DAG || K == HOP_SCHUR_B_DAG) ? 3 : 0;
-    // centre term: 0 none, 1 K5, 2 K5^+, 3 identity, 4 dense K5 B^-1 =
-    // sum_k w_k C^k, 5 its adjoint
+    // centre term: 0 none, 1 K5, 2 K5^+, 3 identity, 4 K5 B^-1,
+    // 5 its adjoint
     static constexpr int cen = (K == HOP_D5 || K == HOP_SCHUR_B) ? 1
                              : (K == HOP_D5_DAG || K == HOP_SCHUR_B_DAG) ? 2
                              : (K == HOP_PREP || K == HOP_SCHUR_B_SYM) ? 3
@@ -394,65 +402,96 @@ template <> struct Raw<P16> {
     }
 };
 
-// Links staged in LDS: 16-byte parts of the 18-real link.  Lane s of a site
-// group copies parts s, s + L5, ... of each of its site's eight links; every
-// lane then reads its site's links back (a broadcast inside the group), so a
-// link crosses the vector-memory path once per site instead of once per lane.
+// Links staged in LDS, one wave's sites at a time.  Lane s of a site group
+// loads the whole link of direction s (L5 >= 8: at most kStageSites sites a
+// wave), so a wave's eight links per site cost 3 / 5 / 9 load instructions
+// (FP16 / FP32 / FP64) where every lane loading every link takes 24 / 40 / 72
+// of its 56 / 88 / 168: the texture addresser spends 18 to 24 cycles on each,
+// whatever its lanes share, and bounds the hop.  Every lane then reads its
+// site's links back from LDS, a broadcast inside the group.  The wave stages
+// its own links, so no workgroup barrier is needed, and the first neighbour's
+// spinor is on its way before the links are waited for.
+// Layout: [direction][16-byte part][site], then the short tails
+// [direction][site].
+constexpr int kStageSites = 8;
 template <Prec P> struct LinkStage;
 template <> struct LinkStage<P64> {
-    static constexpr int NP = 9;
-    static __device__ __forceinline__ void copy_part(const char* seg, size_t lblk, uint32_t idx, int b,
-                                                     unsigned char* dst) {
-        *reinterpret_cast<nd2*>(dst) = ldu<nd2>(seg + b * lblk, idx * 16u);
+    static constexpr int NP = 9, TAIL = 0;
+    nd2 u[9];
+    __device__ __forceinline__ void load(const char* seg, size_t lblk, uint32_t idx) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) u[k] = ldu<nd2>(seg + k * lblk, idx * 16u);
     }
-    static __device__ __forceinline__ void read(const unsigned char* slot, cx<double> U[9]) {
+    __device__ __forceinline__ void put(unsigned char* w, int d, int site) const {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) *reinterpret_cast<nd2*>(w + ((d * NP + k) * kStageSites + site) * 16) = u[k];
+    }
+    static __device__ __forceinline__ void read(const unsigned char* w, int d, int site, cx<double> U[9]) {
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            const nd2 w = reinterpret_cast<const nd2*>(slot)[k];
-            U[k] = {w.x, w.y};
+            const nd2 v = *reinterpret_cast<const nd2*>(w + ((d * NP + k) * kStageSites + site) * 16);
+            U[k] = {v.x, v.y};
         }
     }
 };
 template <> struct LinkStage<P32> {
-    static constexpr int NP = 5;
-    static __device__ __forceinline__ void copy_part(const char* seg, size_t lblk, uint32_t idx, int b,
-                                                     unsigned char* dst) {
-        if (b < 4) *reinterpret_cast<nf4*>(dst) = ldu<nf4>(seg + b * lblk, idx * 16u);
-        else *reinterpret_cast<nf2*>(dst) = ldu<nf2>(seg + 4 * lblk, idx * 8u);
+    static constexpr int NP = 4, TAIL = 8;
+    nf4 u[4];
+    nf2 u8;
+    __device__ __forceinline__ void load(const char* seg, size_t lblk, uint32_t idx) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k] = ldu<nf4>(seg + k * lblk, idx * 16u);
+        u8 = ldu<nf2>(seg + 4 * lblk, idx * 8u);
     }
-    static __device__ __forceinline__ void read(const unsigned char* slot, cx<float> U[9]) {
+    __device__ __forceinline__ void put(unsigned char* w, int d, int site) const {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) *reinterpret_cast<nf4*>(w + ((d * NP + k) * kStageSites + site) * 16) = u[k];
+        *reinterpret_cast<nf2*>(w + 8 * NP * kStageSites * 16 + (d * kStageSites + site) * 8) = u8;
+    }
+    static __device__ __forceinline__ void read(const unsigned char* w, int d, int site, cx<float> U[9]) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const nf4 w = reinterpret_cast<const nf4*>(slot)[k];
-            U[2 * k] = {w.x, w.y};
-            U[2 * k + 1] = {w.z, w.w};
+            const nf4 v = *reinterpret_cast<const nf4*>(w + ((d * NP + k) * kStageSites + site) * 16);
+            U[2 * k] = {v.x, v.y};
+            U[2 * k + 1] = {v.z, v.w};
         }
-        const nf2 w = *reinterpret_cast<const nf2*>(slot + 64);
-        U[8] = {w.x, w.y};
+        const nf2 v = *reinterpret_cast<const nf2*>(w + 8 * NP * kStageSites * 16 + (d * kStageSites + site) * 8);
+        U[8] = {v.x, v.y};
     }
 };
 template <> struct LinkStage<P16> {
-    static constexpr int NP = 3;
-    static __device__ __forceinline__ void copy_part(const char* seg, size_t lblk, uint32_t idx, int b,
-                                                     unsigned char* dst) {
-        if (b < 2) *reinterpret_cast<nu4*>(dst) = ldu<nu4>(seg + b * lblk, idx * 16u);
-        else *reinterpret_cast<uint32_t*>(dst) = ldu<uint32_t>(seg + 2 * lblk, idx * 4u);
+    static constexpr int NP = 2, TAIL = 4;
+    nu4 u[2];
+    uint32_t u8;
+    __device__ __forceinline__ void load(const char* seg, size_t lblk, uint32_t idx) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) u[k] = ldu<nu4>(seg + k * lblk, idx * 16u);
+        u8 = ldu<uint32_t>(seg + 2 * lblk, idx * 4u);
     }
-    static __device__ __forceinline__ void read_h(const unsigned char* slot, h2 U[9]) {
+    __device__ __forceinline__ void put(unsigned char* w, int d, int site) const {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) *reinterpret_cast<nu4*>(w + ((d * NP + k) * kStageSites + site) * 16) = u[k];
+        *reinterpret_cast<uint32_t*>(w + 8 * NP * kStageSites * 16 + (d * kStageSites + site) * 4) = u8;
+    }
+    static __device__ __forceinline__ void read_h(const unsigned char* w, int d, int site, h2 U[9]) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const nu4 w = reinterpret_cast<const nu4*>(slot)[k];
-            U[4 * k] = as_h2(w.x);
-            U[4 * k + 1] = as_h2(w.y);
-            U[4 * k + 2] = as_h2(w.z);
-            U[4 * k + 3] = as_h2(w.w);
+            const nu4 v = *reinterpret_cast<const nu4*>(w + ((d * NP + k) * kStageSites + site) * 16);
+            U[4 * k] = as_h2(v.x);
+            U[4 * k + 1] = as_h2(v.y);
+            U[4 * k + 2] = as_h2(v.z);
+            U[4 * k + 3] = as_h2(v.w);
         }
-        U[8] = as_h2(*reinterpret_cast<const uint32_t*>(slot + 32));
+        U[8] = as_h2(*reinterpret_cast<const uint32_t*>(w + 8 * NP * kStageSites * 16 + (d * kStageSites + site) * 4));
     }
 };
+// bytes of one wave's staged links
+template <Prec P> constexpr int stage_bytes() {
+    return 8 * kStageSites * (LinkStage<P>::NP * 16 + LinkStage<P>::TAIL);
+}
 
 // Accumulate one direction's term from its spinor registers and link.
-template <Prec P, bool DAG, bool PREB, int MU, int DIR>
+template <Prec P, bool DAG, bool PREB, int MU, int DIR, bool FIRST>
 __device__ __forceinline__ void hop_term(cx<typename Real<P>::T> acc[12], const Raw<P>& r,
                                          const cx<typename Real<P>::T> U[9],
                                          const Nbr5<typename Real<P>::T>& nb, typename Real<P>::T b5,
@@ -470,13 +509,13 @@ __device__ __forceinline__ void hop_term(cx<typename Real<P>::T> acc[12], const 
     cx<R> h[6], w[6];
     project<MU>(sg, psi, h);
     su3_mul<(DIR > 0)>(U, h, w);
-    reconstruct_add<MU>(sg, w, acc);
+    reconstruct_add<MU, FIRST>(sg, w, acc);
 }
 
 // FP16 storage: the same term on binary16 pairs (see su3_mul_h); the spinor
 // scale (its norm, or the B pre-hop's common scale) is applied once, in FP32,
 // when the colour product is added to the accumulator.
-template <bool DAG, bool PREB, int MU, int DIR>
+template <bool DAG, bool PREB, int MU, int DIR, bool FIRST>
 __device__ __forceinline__ void hop_term_h(cx<float> acc[12], const Raw<P16>& r, const h2 U[9],
                                            const Nbr5<float>& nb, float b5, float c5) {
     h2 psi[12];
@@ -488,7 +527,7 @@ __device__ __forceinline__ void hop_term_h(cx<float> acc[12], const Raw<P16>& r,
     su3_mul_h<(DIR > 0)>(U, z1, z2, w);
 #pragma unroll
     for (int c = 0; c < 6; ++c) w[c] = scale * w[c];
-    reconstruct_add<MU>(float(sg), w, acc);
+    reconstruct_add<MU, FIRST>(float(sg), w, acc);
 }
 
 // Direction d of the fixed order x+, x-, y+, y-, z+, z-, t+, t-.  Link mode
@@ -496,62 +535,78 @@ __device__ __forceinline__ void hop_term_h(cx<float> acc[12], const Raw<P16>& r,
 // part-holding lanes of the site group (a0: byte address of its first lane).
 template <Prec P, bool DAG, bool PREB, int D, int LM>
 __device__ __forceinline__ void dir_term(cx<typename Real<P>::T> acc[12], const Raw<P>& r,
-                                         const unsigned char* slot, int a0, const Nbr5<typename Real<P>::T>& nb,
+                                         const unsigned char* lw, int sw, int a0, const Nbr5<typename Real<P>::T>& nb,
                                          typename Real<P>::T b5, typename Real<P>::T c5) {
     if constexpr (P == P16) {
         h2 U[9];
-        if constexpr (LM == 1) LinkStage<P16>::read_h(slot, U);
+        if constexpr (LM == 1) LinkStage<P16>::read_h(lw, D, sw, U);
         else if constexpr (LM == 2) r.link_shfl_h(a0, U);
         else r.link_h(U);
-        hop_term_h<DAG, PREB, D / 2, (D % 2 == 0) ? +1 : -1>(acc, r, U, nb, b5, c5);
+        hop_term_h<DAG, PREB, D / 2, (D % 2 == 0) ? +1 : -1, D == 0>(acc, r, U, nb, b5, c5);
     } else {
         cx<typename Real<P>::T> U[9];
-        if constexpr (LM == 1) LinkStage<P>::read(slot, U);
+        if constexpr (LM == 1) LinkStage<P>::read(lw, D, sw, U);
         else if constexpr (LM == 2) r.link_shfl(a0, U);
         else r.link(U);
-        hop_term<P, DAG, PREB, D / 2, (D % 2 == 0) ? +1 : -1>(acc, r, U, nb, b5, c5);
+        hop_term<P, DAG, PREB, D / 2, (D % 2 == 0) ? +1 : -1, D == 0>(acc, r, U, nb, b5, c5);
     }
 }
 
-// Link modes (see dir_term): the LDS stage needs at most kStageSites sites per
-// wave (L5 >= 8), the lane gather needs L5 >= the number of 16-byte parts.
-constexpr int kStageSites = 8;
+// LDS tile of five_lanes: six components of a wave's lanes, the components one
+// element further apart than the lanes so that the lanes of its recurrence
+// fall into different banks
+constexpr int kFivePitch = 64 + 1;
+template <typename R> constexpr int five_bytes() { return 6 * kFivePitch * int(sizeof(cx<R>)); }
 
-// Hop kinds with a dense fifth-dimension polynomial as their centre term
-template <int K> constexpr bool dense_centre() { return HopTraits<K>::cen == 4 || HopTraits<K>::cen == 5; }
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-// out = sum_j T[s][j] v_j across the L5 lanes of each site (lane s of the
-// site's group holds slice s), with ct = T[s] the lane's row of coefficient
-// pairs (P+ components use .re, P- components .im).  The values go through
-// an LDS tile of six components per thread in two passes, the P+ spins and
-// then the P- spins; every thread of the workgroup calls this (barriers).
-template <typename R>
-__device__ __forceinline__ void dense_poly_lanes(const cx<R> v[12], cx<R> out[12], cx<R>* tile, const cx<R>* ct,
-                                                 int tid, int s, int L5, bool valid) {
-    const cx<R>* col = tile + (tid - s);
+// A fifth-dimension operator O in place on v, lane s of a site's group holding
+// slice s.  O is B K5^-1, K5^-1 or K5 B^-1, i.e. (p + q C)(1 - z C)^-1, so on
+// one component it is a recurrence along the slices in the direction C moves
+// that chirality (the adjoint: the other way), across the wall with -m_q:
+//   e' = v_s + z e,  out_s = A v_s + B e,  starting from e = w T,
+//   T = sum_s z^(L5-1-s) v_s,  w = -m_q / (1 + m_q z^L5);  rec = (A, B, z, w).
+// |z| < 1 for every accepted action (b5 > c5 >= 0, M5 < 2), so rounding errors
+// do not grow along it.
+// Four operations a slice and component, where the dense L5 x L5 sum takes L5
+// and (in the lanes' own slices) the index arithmetic of every term.  The
+// values go through an LDS tile, the P+ spins and then the P- spins, and lane
+// 6 i + c runs component c of the wave's site i; a site's lanes are one wave's,
+// so no workgroup barrier is needed.  At L5 = 8 this takes 170 vector
+// instructions for kernel A's 396 of the dense sum.
+template <bool ADJ, typename R>
+__device__ __forceinline__ void five_lanes(cx<R> v[12], cx<R>* tile, const double* rec, int lane, int L5, int spw) {
+    const R A = R(rec[0]), B = R(rec[1]), z = R(rec[2]), w = R(rec[3]);
+    wave_sync();   // the tile's bytes may hold the wave's links until here
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-        if (half) __syncthreads();   // every lane is done with the P+ pass
 #pragma unroll
-        for (int c = 0; c < 6; ++c) tile[c * kBlock + tid] = v[6 * half + c];
-        __syncthreads();
-        if (valid) {
-            {
-                const cx<R> f = ct[0];
-                const R fh = half ? f.im : f.re;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) out[6 * half + c] = fh * col[c * kBlock];
-            }
-            // rolled: the six component reads share one address with
-            // immediate offsets
-#pragma unroll 1
-            for (int j = 1; j < L5; ++j) {
-                const cx<R> f = ct[j];
-                const R fh = half ? f.im : f.re;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) out[6 * half + c] = out[6 * half + c] + fh * col[c * kBlock + j];
+        for (int c = 0; c < 6; ++c) tile[c * kFivePitch + lane] = v[6 * half + c];
+        wave_sync();
+        const bool up = (half == 0) != ADJ;   // slice s reads s - 1
+        for (int e = lane; e < 6 * spw; e += 64) {
+            const int i = int((uint32_t(e) * 10923u) >> 16), c = e - 6 * i;   // e / 6 (e < 384)
+            cx<R>* col = tile + c * kFivePitch + i * L5 + (up ? 0 : L5 - 1);
+            const int st = up ? 1 : -1;
+            cx<R> T = col[0];
+#pragma unroll 4
+            for (int k = 1; k < L5; ++k) T = col[k * st] + z * T;
+            cx<R> f = w * T;
+#pragma unroll 4
+            for (int k = 0; k < L5; ++k) {
+                const cx<R> x = col[k * st];
+                col[k * st] = A * x + B * f;
+                f = x + z * f;
             }
         }
+        wave_sync();
+#pragma unroll
+        for (int c = 0; c < 6; ++c) v[6 * half + c] = tile[c * kFivePitch + lane];
+        if (half == 0) wave_sync();
     }
 }
 // 16-byte parts gathered by lane exchange (the short tail is loaded by every lane)

@@ -100,14 +100,16 @@ struct Geo {
 };
 
 // Coefficients of one right-hand side (its mass); all fifth-dimension
-// operators are polynomials in C: sum_k c_k C^k.
+// operators are polynomials in C: sum_k c_k C^k, and those inside the hop
+// kernels recurrences along the slices.
 struct RhsCoef {
     double mq, b5, c5;
     double k5[2];         // K5 = k5[0] + k5[1] C
-    double m[kMaxL5];     // B K5^-1   = sum_k m[k] C^k
     double kinv[kMaxL5];  // K5^-1     = sum_k kinv[k] C^k
-    double w[kMaxL5];     // K5 B^-1   = sum_k w[k] C^k
     double binv[kMaxL5];  // B^-1      = sum_k binv[k] C^k
+    // The hop kernels' operators as recurrences along the slices (see
+    // five_lanes): B K5^-1 (K5^-1 in the symmetric form's table) and K5 B^-1
+    double rm[4], rw[4];
 };
 
 // Bytes of a native half field / link segment.
@@ -197,8 +199,21 @@ __device__ __forceinline__ void unpack_h2(uint32_t w, float s, cx<float>& c) {
     c.re = h2f(w & 0xffffu) * s;
     c.im = h2f(w >> 16) * s;
 }
+// c * inv as a binary16 pair.  The empty asm keeps the two conversions apart,
+// so that each is one v_fma_mix writing its half of the word (converted as a
+// pair they cost a shift and an or more).
 __device__ __forceinline__ uint32_t pack_h2(cx<float> c, float inv) {
-    return f2h(c.re * inv) | (f2h(c.im * inv) << 16);
+    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+    _Float16 re = _Float16(c.re * inv);
+    asm("" : "+v"(re));
+    return __builtin_bit_cast(uint32_t, half2v{re, _Float16(c.im * inv)});
+}
+// max(n, |a|, |b|), ignoring NaN like fmaxf; written as the instruction,
+// since the compiler first quiets every operand with an instruction of its own
+__device__ __forceinline__ float max3_abs(float n, float a, float b) {
+    float r;
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(n), "v"(a), "v"(b));
+    return r;
 }
 
 template <> struct Field<P16> {
@@ -223,9 +238,39 @@ template <> struct Field<P16> {
     // stored as zero (its reciprocal would overflow); NaN propagates.
     template <bool NT = false>
     static __device__ __forceinline__ void store(void* base, int Vh, int j, cx<R> v[12]) {
+        nu4 w[3];
+        const float n = store_raw<NT>(base, Vh, j, v, w);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            unpack_h2(w[k].x, n, v[4 * k]);
+            unpack_h2(w[k].y, n, v[4 * k + 1]);
+            unpack_h2(w[k].z, n, v[4 * k + 2]);
+            unpack_h2(w[k].w, n, v[4 * k + 3]);
+        }
+    }
+    // the same without replacing v; returns |stored value|^2 of the site
+    template <bool NT = false>
+    static __device__ __forceinline__ double store_norm2(void* base, int Vh, int j, const cx<R> v[12]) {
+        nu4 w[3];
+        const float n = store_raw<NT>(base, Vh, j, v, w);
+        typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+        float a = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const uint32_t u = w[k][m];
+                const half2v h = __builtin_bit_cast(half2v, u);
+                a = __builtin_amdgcn_fdot2(h, h, a, false);
+            }
+        return double(a) * (double(n) * double(n));
+    }
+    // stores v; w is the stored halves, the return value their norm
+    template <bool NT>
+    static __device__ __forceinline__ float store_raw(void* base, int Vh, int j, const cx<R> v[12], nu4 w[3]) {
         float n = 0.f;
 #pragma unroll
-        for (int k = 0; k < 12; ++k) n = fmaxf(n, fmaxf(fabsf(v[k].re), fabsf(v[k].im)));
+        for (int k = 0; k < 12; ++k) n = max3_abs(n, v[k].re, v[k].im);
         float inv = __builtin_amdgcn_rcpf(n);   // scale into [-1, 1] before rounding
         if (n < 1.17549435e-38f) {
             n = 0.f;
@@ -235,19 +280,15 @@ template <> struct Field<P16> {
         float* nrm = reinterpret_cast<float*>(static_cast<char*>(base) + norm_offset(Vh));
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            nu4 w;
-            w.x = pack_h2(v[4 * k], inv);
-            w.y = pack_h2(v[4 * k + 1], inv);
-            w.z = pack_h2(v[4 * k + 2], inv);
-            w.w = pack_h2(v[4 * k + 3], inv);
-            st16<NT>(p + size_t(k) * Vh + j, w);
-            unpack_h2(w.x, n, v[4 * k]);
-            unpack_h2(w.y, n, v[4 * k + 1]);
-            unpack_h2(w.z, n, v[4 * k + 2]);
-            unpack_h2(w.w, n, v[4 * k + 3]);
+            w[k].x = pack_h2(v[4 * k], inv);
+            w[k].y = pack_h2(v[4 * k + 1], inv);
+            w[k].z = pack_h2(v[4 * k + 2], inv);
+            w[k].w = pack_h2(v[4 * k + 3], inv);
+            st16<NT>(p + size_t(k) * Vh + j, w[k]);
         }
         if (NT) __builtin_nontemporal_store(n, nrm + j);
         else nrm[j] = n;
+        return n;
     }
 };
 
