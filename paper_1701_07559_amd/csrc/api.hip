@@ -438,24 +438,43 @@ mdwf_status mdwf_create(const mdwf_geometry* geom, int hip_device, void* hip_str
     g.fXh = FastDiv(uint32_t(g.Xh));
     g.fY = FastDiv(uint32_t(g.Y));
     g.fZ = FastDiv(uint32_t(g.Z));
-    // default launch shape (mdwf_autotune refines it per precision): z-blocks
-    // of 4 (or 2) planes with t inside; links staged in LDS (L5 >= 8; against
-    // every lane loading them: FP32 hop 316 -> 277 us and FP64 S 1383 -> 1284 us
-    // at 24^3 x 64, L5 = 8, and no shape measured slower).  The MDWF_TILE
-    // ("bx,by,bz,bt"), MDWF_XCD_REMAP, MDWF_NT_STORE, MDWF_LINK_MODE and
-    // MDWF_RHS_GROUP variables override it
-    mdwf_launch_tune t0{{g.Xh, g.Y, (g.Z % 4 == 0) ? 4 : 2, 1}, 1, 0, 1, 0, 0.0, 0};
+    // default launch shape (mdwf_autotune refines it per precision; the
+    // MDWF_TILE ("bx,by,bz,bt"), MDWF_XCD_REMAP, MDWF_NT_STORE, MDWF_LINK_MODE
+    // and MDWF_RHS_GROUP variables override it):
+    //  - eight spatial columns marched along t, one per XCD, so that none cuts
+    //    a tile and each one's time planes stay in its L2 (FP64 S at 24^3 x 64,
+    //    L5 = 8: 1174 us for 1259 us with six z-blocks; FP32 hop 254 for 271).
+    //    Columns of fewer than 192 sites a plane, or extents they don't divide,
+    //    keep z-blocks of 4 (or 2) planes with t inside (three FP32 RHS at
+    //    12^3 x 24: 56.0 ms a solve for 57.8 ms)
+    //  - links staged in LDS (L5 >= 8; against every lane loading them: FP32
+    //    hop 316 -> 277 us, FP64 S 1383 -> 1284 us at 24^3 x 64, no shape slower)
+    //  - one right-hand side after the other: a tile's together share its links
+    //    but evict each other's neighbours from L2 (FP16, twelve at
+    //    24^3 x 32, L5 = 10: 5068 us for 5660 us; six FP64 at 16^3 x 32, 2049 for 2287)
+    //  - FP16 results stored past L2, which the next kernel's first reads don't
+    //    find there either way (twelve at 24^3 x 64: 7550 us for 7730 us; FP32 and FP64
+    //    measure the same)
+    mdwf_launch_tune t0{{g.Xh, g.Y, (g.Z % 4 == 0) ? 4 : 2, 1}, 1, 0, 1, 1, 0.0, 0};
+    if (g.Z % 4 == 0 && g.Xh * (g.Y / 2) * (g.Z / 4) >= 192) {
+        t0.tile[1] = g.Y / 2;
+        t0.tile[2] = g.Z / 4;
+        t0.tile[3] = 2;
+    }
     if (const char* e = std::getenv("MDWF_TILE")) {
         int b[4];
         if (std::sscanf(e, "%d,%d,%d,%d", &b[0], &b[1], &b[2], &b[3]) == 4 && tile_fits(g, b))
             for (int k = 0; k < 4; ++k) t0.tile[k] = b[k];
     }
     if (const char* e = std::getenv("MDWF_XCD_REMAP")) t0.xcd_remap = std::atoi(e) != 0;
-    if (const char* e = std::getenv("MDWF_NT_STORE")) t0.nt_store = std::atoi(e) != 0;
+    const char* nt = std::getenv("MDWF_NT_STORE");
     if (const char* e = std::getenv("MDWF_LINK_MODE")) t0.link_mode = std::atoi(e);
     if (const char* e = std::getenv("MDWF_RHS_GROUP")) t0.rhs_group = std::atoi(e);
     if (const char* e = std::getenv("MDWF_PLANE_BT")) t0.plane_bt = std::atoi(e);
-    for (int p = 0; p < 3; ++p) set_tune(g, Prec(p), t0);
+    for (int p = 0; p < 3; ++p) {
+        t0.nt_store = nt ? std::atoi(nt) != 0 : p == P16;
+        set_tune(g, Prec(p), t0);
+    }
     scratch_init(hip_device);   // the device address of this device's static scratch
     if (hipMalloc(&c->d_coef1, 2 * sizeof(RhsCoef)) != hipSuccess) {
         (void)hipGetLastError();

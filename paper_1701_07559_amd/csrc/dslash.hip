@@ -26,17 +26,17 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     using TR = HopTraits<K>;
     const int L5 = g.L5;
     const int spw = 64 / L5;
-    const int lb = g.xcd_remap[P] ? xcd_logical_block(blockIdx.x, gridDim.x) : int(blockIdx.x);
-    // RHS groups of rg: the blocks of one group sweep the tiles with the
-    // group's RHS fastest (they share each tile's links in L2); groups follow
-    // each other, so a spinor's neighbour reuse spans rg RHS, not all of them
+    // RHS groups of rg follow each other; within one, every XCD sweeps its own
+    // range of tiles, the group's RHS fastest (they share each tile's links in
+    // L2, and its neighbour reuse spans rg RHS, not all of them)
     int rhs, tile;
     {
         const int rg = (g.rhs_group[P] > 0 && g.rhs_group[P] < a.nrhs) ? g.rhs_group[P] : a.nrhs;
-        const int grp = lb / (a.nblk * rg);
+        const int grp = int(blockIdx.x) / (a.nblk * rg);
         const int base = grp * rg;
         const int gs = min(rg, a.nrhs - base);
-        const int off = lb - grp * a.nblk * rg;
+        int off = int(blockIdx.x) - grp * a.nblk * rg;
+        if (g.xcd_remap[P]) off = xcd_logical_block(off, a.nblk * gs);
         tile = off / gs;
         rhs = base + (off - tile * gs);
     }
