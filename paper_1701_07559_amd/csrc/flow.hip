@@ -9,12 +9,12 @@
 // in its low-storage form: per stage i, E_i = a_i eps Z(W_i) + b_i E_{i-1}
 // and W_{i+1} = exp(E_i) W_i with (a, b) = (1/4, 0), (8/9, -17/9), (3/4, -1).
 //
-// One kernel launch per stage: a thread per link reads the stage's input
-// field (the link and its six staples; staple links by their first two
-// rows), writes E_i for that link (its eight independent reals) and the
-// updated link into a second buffer, so every staple sees the stage's input.
-// The exponential of the small traceless antihermitian E is a degree-12
-// Taylor polynomial after scaling by a power of two with squaring back.
+// One kernel launch per stage, on fields laid out [mu][entry][site] between the
+// first and the last: a wave owns one direction of 64 consecutive sites, so each
+// of its loads is 64 adjacent entries.  A thread reads the stage's input field
+// (its link and the six staples; staple links by their first two rows), writes
+// E_i for that link (its eight independent reals) and the updated link into a
+// second buffer, so every staple sees the stage's input.
 #include <cmath>
 #include <cstdio>
 #include <vector>
@@ -32,14 +32,19 @@ struct Su3 {
     cx<double> m[9];
 };
 
+__device__ __forceinline__ cx<double> ld(const double2* p) {
+    const double2 v = *p;
+    return {v.x, v.y};
+}
+// stored past L2, which the stage's links need
+__device__ __forceinline__ void st_past(double2* p, double a, double b) {
+    __builtin_nontemporal_store(nd2{a, b}, reinterpret_cast<nd2*>(p));
+}
 __device__ __forceinline__ Su3 ld_link(const double2* U, long link) {
     Su3 r;
     const double2* p = U + link * 9;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const double2 v = p[k];
-        r.m[k] = {v.x, v.y};
-    }
+    for (int k = 0; k < 9; ++k) r.m[k] = ld(p + k);
     return r;
 }
 
@@ -52,18 +57,10 @@ __device__ __forceinline__ cx<double> conj_cross(cx<double> a, cx<double> b, cx<
     const cx<double> v = cmadd(cmul(a, b), cx<double>{-c.re, -c.im}, d);   // a b - c d
     return {v.re, -v.im};
 }
-__device__ __forceinline__ Su3 ld_link12(const double2* U, long link) {
-    Su3 r;
-    const double2* p = U + link * 9;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const double2 v = p[k];
-        r.m[k] = {v.x, v.y};
-    }
+__device__ __forceinline__ void third_row(Su3& r) {
     r.m[6] = conj_cross(r.m[1], r.m[5], r.m[2], r.m[4]);
     r.m[7] = conj_cross(r.m[2], r.m[3], r.m[0], r.m[5]);
     r.m[8] = conj_cross(r.m[0], r.m[4], r.m[1], r.m[3]);
-    return r;
 }
 
 // The Runge-Kutta accumulator E is traceless antihermitian: eight reals per
@@ -77,33 +74,7 @@ __device__ __forceinline__ void complete_alg(Su3& r) {
     r.m[6] = {-r.m[2].re, r.m[2].im};
     r.m[7] = {-r.m[5].re, r.m[5].im};
 }
-__device__ __forceinline__ Su3 ld_alg(const double2* E, long link) {
-    const double2* p = E + link * 4;
-    const double2 d = p[0], e01 = p[1], e02 = p[2], e12 = p[3];
-    Su3 r;
-    r.m[0] = {0.0, d.x};
-    r.m[4] = {0.0, d.y};
-    r.m[1] = {e01.x, e01.y};
-    r.m[2] = {e02.x, e02.y};
-    r.m[5] = {e12.x, e12.y};
-    complete_alg(r);
-    return r;
-}
-__device__ __forceinline__ void st_alg(double2* E, long link, const Su3& a) {
-    double2* p = E + link * 4;
-    p[0] = make_double2(a.m[0].im, a.m[4].im);
-    p[1] = make_double2(a.m[1].re, a.m[1].im);
-    p[2] = make_double2(a.m[2].re, a.m[2].im);
-    p[3] = make_double2(a.m[5].re, a.m[5].im);
-}
-
-__device__ __forceinline__ void st_link(double2* U, long link, const Su3& a) {
-    double2* p = U + link * 9;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) p[k] = make_double2(a.m[k].re, a.m[k].im);
-}
-
-// a b, a^+ b, a b^+
+// a b, a b^+
 __device__ __forceinline__ Su3 mul(const Su3& a, const Su3& b) {
     Su3 r;
 #pragma unroll
@@ -113,19 +84,6 @@ __device__ __forceinline__ Su3 mul(const Su3& a, const Su3& b) {
             cx<double> s = {0.0, 0.0};
 #pragma unroll
             for (int k = 0; k < 3; ++k) s = cmadd(s, a.m[i * 3 + k], b.m[k * 3 + j]);
-            r.m[i * 3 + j] = s;
-        }
-    return r;
-}
-__device__ __forceinline__ Su3 mul_dn(const Su3& a, const Su3& b) {   // a^+ b
-    Su3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            cx<double> s = {0.0, 0.0};
-#pragma unroll
-            for (int k = 0; k < 3; ++k) s = cjmadd(s, a.m[k * 3 + i], b.m[k * 3 + j]);
             r.m[i * 3 + j] = s;
         }
     return r;
@@ -149,31 +107,54 @@ __device__ __forceinline__ Su3 mul_nd(const Su3& a, const Su3& b) {   // a b^+
 
 // exp(X) for a traceless antihermitian X: scale by 2^-k until the Frobenius
 // norm is at most 1/4, Taylor polynomial of degree 12 by Horner's rule, then
-// square k times (truncation below 1e-17 relative)
-__device__ Su3 expm_small(Su3 X) {
-    double n2 = 0.0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) n2 += X.m[k].re * X.m[k].re + X.m[k].im * X.m[k].im;
+// square k times (truncation below 1e-17 relative).  By Cayley and Hamilton
+// X^3 = t X + det X with t = tr X^2 / 2 real and det X = i e imaginary, so
+// Horner's R = 1 + X R / d runs on the three complex coefficients of
+// R = r0 + r1 X + r2 X^2: some ten operations a step for a product of matrices.
+__device__ __forceinline__ Su3 expm_small(Su3 X) {
+    // off-diagonal moduli; X_kk = i a_k
+    auto n2 = [](cx<double> v) { return v.re * v.re + v.im * v.im; };
+    double t = -0.5 * (X.m[0].im * X.m[0].im + X.m[4].im * X.m[4].im + X.m[8].im * X.m[8].im) -
+               (n2(X.m[1]) + n2(X.m[2]) + n2(X.m[5]));
     int sq = 0;
     double scale = 1.0;
-    const double n = sqrt(n2);
+    const double n = sqrt(-2.0 * t);
     while (n * scale > 0.25 && sq < 40) {
         scale *= 0.5;
         ++sq;
     }
 #pragma unroll
     for (int k = 0; k < 9; ++k) X.m[k] = scale * X.m[k];
-    Su3 R;
+    t *= scale * scale;
+    const double a0 = X.m[0].im, a1 = X.m[4].im, a2 = X.m[8].im;
+    const double n01 = n2(X.m[1]), n02 = n2(X.m[2]), n12 = n2(X.m[5]);
+    const cx<double> p = cmul(X.m[1], X.m[5]);   // X01 X12
+    // det X = i e
+    const double e = a0 * n12 + a1 * n02 + a2 * n01 - a0 * a1 * a2 - 2.0 * (p.im * X.m[2].re - p.re * X.m[2].im);
+    // X^2, hermitian
+    const double d0 = -(a0 * a0 + n01 + n02), d1 = -(a1 * a1 + n01 + n12), d2 = -(a2 * a2 + n02 + n12);
+    auto ti = [](double a, cx<double> v) { return cx<double>{-a * v.im, a * v.re}; };   // i a v
+    auto cj = [](cx<double> v) { return cx<double>{v.re, -v.im}; };
+    const cx<double> q01 = cmadd(ti(a0 + a1, X.m[1]), X.m[2], X.m[7]);
+    const cx<double> q02 = ti(a0 + a2, X.m[2]) + p;
+    const cx<double> q12 = cmadd(ti(a1 + a2, X.m[5]), X.m[3], X.m[2]);
+    cx<double> r0 = {1.0, 0.0}, r1 = {0.0, 0.0}, r2 = {0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < 9; ++k) R.m[k] = {(k % 4 == 0) ? 1.0 : 0.0, 0.0};
-    for (int d = 12; d >= 1; --d) {   // R = 1 + X R / d
-        Su3 t = mul(X, R);
+    for (int d = 12; d >= 1; --d) {
         const double inv = 1.0 / d;
+        const cx<double> s1 = inv * (r0 + t * r2);
+        r0 = {1.0 - inv * e * r2.im, inv * e * r2.re};
+        r2 = inv * r1;
+        r1 = s1;
+    }
+    Su3 R;
+    const cx<double> q[9] = {{d0, 0.0}, q01, q02, cj(q01), {d1, 0.0}, q12, cj(q02), cj(q12), {d2, 0.0}};
 #pragma unroll
-        for (int k = 0; k < 9; ++k) R.m[k] = inv * t.m[k];
-        R.m[0].re += 1.0;
-        R.m[4].re += 1.0;
-        R.m[8].re += 1.0;
+    for (int k = 0; k < 9; ++k) {
+        cx<double> v = cmul(r1, X.m[k]);
+        if (k % 4 == 0) v = v + r0 + q[k].re * r2;
+        else v = cmadd(v, r2, q[k]);
+        R.m[k] = v;
     }
     for (int s = 0; s < sq; ++s) R = mul(R, R);
     return R;
@@ -191,62 +172,235 @@ __device__ __forceinline__ long nbr(const FlowGeo& g, int x, int y, int z, int t
     return long(x) + long(g.X) * (y + long(g.Y) * (z + long(g.Z) * t));
 }
 
-// one Runge-Kutta stage for every link: E = a Z(Win) + b E, Wout = exp(E) Win
-__global__ void __launch_bounds__(kFlowBlock) k_flow_stage(const FlowGeo g, const double2* Win, double2* Wout,
-                                                           double2* E, double a, double b, long nlinks) {
-    const long l = long(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (l >= nlinks) return;
-    const int mu = int(l & 3);
-    const long site = l >> 2;
-    const int x = int(site % g.X);
-    const int y = int((site / g.X) % g.Y);
-    const int z = int((site / (long(g.X) * g.Y)) % g.Z);
-    const int t = int(site / (long(g.X) * g.Y * g.Z));
-    const long xp = nbr(g, x, y, z, t, mu, 1);
+__device__ __forceinline__ uint32_t sel4(int d, int a, int b, int c, int e) {
+    int v = d == 1 ? b : a;
+    v = d == 2 ? c : v;
+    return uint32_t(d == 3 ? e : v);
+}
+
+constexpr int kFlowSites = 64;    // sites of a workgroup, one per lane; a wave per direction
+constexpr int kSitePitch = 37;    // double2 of a site's four links in LDS, padded off the banks
+
+// Traversal of a stage: slabs of bz planes, t inside, then z, y, x; every XCD
+// sweeps one contiguous part, so a slab's time planes stay in its L2.
+struct FlowTrav {
+    FastDiv slab, plane, xy, x;   // sites of a slab (bz planes), of one time plane of it, X Y, X
+    int bz;
+    uint32_t nsites;
+};
+
+// one Runge-Kutta stage for every link: E = a Z(Win) + b E, Wout = exp(E) Win.
+// CANON: Wout in the canonical layout (through LDS), otherwise [mu][entry][site].
+//
+// A link's six staples take 18 neighbouring links.  Read from the canonical
+// layout each lane of a load touches its own cache line; that, the address
+// unit's rate, and products of full matrices made this stage 1077 us at
+// 24^3 x 64.  Here adjacent lanes read adjacent entries, only two rows of every
+// SU(3) product are computed, and the four directions of a site, a wave each,
+// share what they can through LDS: U_nu(x), U_nu(x-nu) (three waves) and
+// U_nu(x+mu) (the waves of mu and nu, which go through the planes in step).
+// That leaves 73 loads a link of 121, and some 430 us, FP64 issue busy
+// over half the time.
+// Three waves a SIMD (168 registers, 48 KB a workgroup) are worth more than
+// loads ahead of their use: with the next staple's in flight, 204 registers
+// and two waves, it runs 9 % slower.
+template <bool CANON>
+__global__ void __launch_bounds__(4 * kFlowSites) k_flow_stage(const FlowGeo g, const FlowTrav tv, const double2* Win,
+                                                               double2* Wout, double2* E, double a, double b) {
+    __shared__ double2 lds[2 * 24 * kFlowSites];
+    double2* own = lds;                       // [mu][entry][lane]: rows of U_mu(x)
+    double2* ex = lds + 24 * kFlowSites;      // of U_mu(x-mu), then of the links the waves exchange
+    const int lane = threadIdx.x & 63;
+    const int mu = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const uint32_t V = tv.nsites;
+    const uint32_t first = uint32_t(xcd_logical_block(blockIdx.x, gridDim.x)) * kFlowSites;
+    const bool valid = first + lane < V;
+    const uint32_t pos = valid ? first + lane : V - 1;   // idle lanes repeat the last site, storing nothing
+    const uint32_t sl = tv.slab.div(pos), in = pos - sl * tv.slab.d;
+    const int z0 = int(sl) * tv.bz;
+    // the last slab may be thinner
+    const bool whole = z0 + tv.bz <= g.Z;
+    const uint32_t pl = whole ? tv.plane.d : uint32_t(g.Z - z0) * tv.xy.d;
+    const int t = int(whole ? tv.plane.div(in) : in / pl);
+    const uint32_t r = in - uint32_t(t) * pl;
+    const uint32_t zz = tv.xy.div(r), r2 = r - zz * tv.xy.d;
+    const int y = int(tv.x.div(r2)), x = int(r2 - uint32_t(y) * tv.x.d), z = z0 + int(zz);
+    const int sy = g.X, sz = g.X * g.Y, sT = sz * g.Z;
+    const uint32_t site = uint32_t(x + sy * y + sz * z) + uint32_t(sT) * uint32_t(t);
+    // site offsets of the neighbours
+    const int f0 = x == g.X - 1 ? 1 - g.X : 1, f1 = y == g.Y - 1 ? (1 - g.Y) * sy : sy;
+    const int f2 = z == g.Z - 1 ? (1 - g.Z) * sz : sz, f3 = t == g.T - 1 ? (1 - g.T) * sT : sT;
+    const int b0 = x == 0 ? g.X - 1 : -1, b1 = y == 0 ? (g.Y - 1) * sy : -sy;
+    const int b2 = z == 0 ? (g.Z - 1) * sz : -sz, b3 = t == 0 ? (g.T - 1) * sT : -sT;
+    auto entry = [&](int d, int k, uint32_t i) {
+        return ld(reinterpret_cast<const double2*>(reinterpret_cast<const char*>(Win + size_t(d * 9 + k) * V) +
+                                                   i * 16u));
+    };
+    auto rows = [&](int d, uint32_t i) {   // the first two rows
+        Su3 r;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) r.m[k] = entry(d, k, i);
+        return r;
+    };
+    auto put = [&](double2* p, int d, const Su3& v) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) p[(d * 6 + k) * kFlowSites + lane] = make_double2(v.m[k].re, v.m[k].im);
+    };
+    auto get = [&](const double2* p, int d) {
+        Su3 r;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) r.m[k] = ld(p + (d * 6 + k) * kFlowSites + lane);
+        return r;
+    };
+    const uint32_t xp = site + sel4(mu, f0, f1, f2, f3);
+    put(ex, mu, rows(mu, site + sel4(mu, b0, b1, b2, b3)));
+    put(own, mu, rows(mu, site));
+    __syncthreads();
     Su3 S;
 #pragma unroll
     for (int k = 0; k < 9; ++k) S.m[k] = {0.0, 0.0};
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
-        // upper staple U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
-        const long xn = nbr(g, x, y, z, t, nu, 1);
-        Su3 s1 = mul_nd(ld_link12(Win, xp * 4 + nu), ld_link12(Win, xn * 4 + mu));
-        s1 = mul_nd(s1, ld_link12(Win, site * 4 + nu));
-        // lower staple U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu)
-        const long xm = nbr(g, x, y, z, t, nu, -1);
-        int cx_[4] = {x, y, z, t};
-        cx_[nu] = (cx_[nu] - 1 + (nu == 0 ? g.X : nu == 1 ? g.Y : nu == 2 ? g.Z : g.T)) %
-                  (nu == 0 ? g.X : nu == 1 ? g.Y : nu == 2 ? g.Z : g.T);
-        const long xpm = nbr(g, cx_[0], cx_[1], cx_[2], cx_[3], mu, 1);
-        const Su3 a1 = ld_link12(Win, xpm * 4 + nu);
-        const Su3 a2 = ld_link12(Win, xm * 4 + mu);
-        // (U_mu(x-nu) U_nu(x+mu-nu))^+ U_nu(x-nu)
-        Su3 s2 = mul(a2, a1);
-        s2 = mul_dn(s2, ld_link12(Win, xm * 4 + nu));
+    // a staple is in SU(3): its third row follows from the first two, as a link's does
+#pragma unroll 1
+    for (int j = 1; j < 4; ++j) {   // lower staples (U_mu(x-nu) U_nu(x+mu-nu))^+ U_nu(x-nu)
+        const int nu = mu ^ j;
+        const uint32_t dn = sel4(nu, b0, b1, b2, b3);
+        Su3 A = rows(nu, xp + dn), B = rows(mu, site + dn), C = get(ex, nu);
+        third_row(B);
+        A.m[6] = conj_cross(A.m[1], A.m[5], A.m[2], A.m[4]);
+        A.m[7] = conj_cross(A.m[2], A.m[3], A.m[0], A.m[5]);
+        cx<double> Q[6];   // the first two columns of U_mu U_nu
 #pragma unroll
-        for (int k = 0; k < 9; ++k) S.m[k] = S.m[k] + s1.m[k] + s2.m[k];
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                cx<double> v = {0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < 3; ++k) v = cmadd(v, B.m[l * 3 + k], A.m[k * 3 + i]);
+                Q[i * 3 + l] = v;
+            }
+        third_row(C);
+        Su3 s2;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                cx<double> v = {0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < 3; ++k) v = cjmadd(v, Q[i * 3 + k], C.m[k * 3 + l]);
+                s2.m[i * 3 + l] = v;
+            }
+        third_row(s2);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) S.m[k] = S.m[k] + s2.m[k];
     }
-    const Su3 U = ld_link(Win, l);
+#pragma unroll 1
+    for (int j = 1; j < 4; ++j) {   // upper staples U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
+        const int nu = mu ^ j;
+        const Su3 A = rows(nu, xp);   // the wave of nu needs it too and loads U_mu(x+nu)
+        __syncthreads();
+        put(ex, mu, A);
+        __syncthreads();
+        Su3 B = get(ex, nu), C = get(own, nu);
+        third_row(B);
+        cx<double> P[6];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                cx<double> v = {0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < 3; ++k) v = cjmadd(v, B.m[l * 3 + k], A.m[i * 3 + k]);
+                P[i * 3 + l] = v;
+            }
+        third_row(C);
+        Su3 s1;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                cx<double> v = {0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < 3; ++k) v = cjmadd(v, C.m[l * 3 + k], P[i * 3 + k]);
+                s1.m[i * 3 + l] = v;
+            }
+        third_row(s1);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) S.m[k] = S.m[k] + s1.m[k];
+    }
+    Su3 U = get(own, mu);
+#pragma unroll
+    for (int k = 6; k < 9; ++k) U.m[k] = entry(mu, k, site);
     const Su3 O = mul(U, S);
-    // Z = -1/2 (O - O^+) + 1/6 tr(O - O^+); tr(O - O^+) = 2 i Im tr O
-    const double itr = (O.m[0].im + O.m[4].im + O.m[8].im) / 3.0;
-    // the eight independent entries of E (upper triangle, first two
+    // Z = -1/2 (O - O^+) + 1/6 tr(O - O^+); tr(O - O^+) = 2 i Im tr O.
+    // The eight independent entries of E (upper triangle, first two
     // diagonal ones); the rest follow from antihermiticity and zero trace
-    Su3 Ev = (b != 0.0) ? ld_alg(E, l) : Su3{};
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = i; j < 3; ++j) {
-            if (i == 2) continue;
-            const cx<double> oij = O.m[i * 3 + j], oji = O.m[j * 3 + i];
-            cx<double> zij = {-0.5 * (oij.re - oji.re), -0.5 * (oij.im + oji.im)};
-            if (i == j) zij.im += itr;
-            const cx<double> prev = (b != 0.0) ? Ev.m[i * 3 + j] : cx<double>{0.0, 0.0};
-            Ev.m[i * 3 + j] = {a * zij.re + b * prev.re, a * zij.im + b * prev.im};
-        }
-    st_alg(E, l, Ev);
+    const double itr = (O.m[0].im + O.m[4].im + O.m[8].im) / 3.0;
+    Su3 Ev;
+    double2* Ep = E + size_t(mu * 4) * V + site;
+    Ev.m[0] = {0.0, a * (itr - O.m[0].im)};
+    Ev.m[4] = {0.0, a * (itr - O.m[4].im)};
+    Ev.m[1] = {-0.5 * a * (O.m[1].re - O.m[3].re), -0.5 * a * (O.m[1].im + O.m[3].im)};
+    Ev.m[2] = {-0.5 * a * (O.m[2].re - O.m[6].re), -0.5 * a * (O.m[2].im + O.m[6].im)};
+    Ev.m[5] = {-0.5 * a * (O.m[5].re - O.m[7].re), -0.5 * a * (O.m[5].im + O.m[7].im)};
+    if (b != 0.0 && valid) {
+        const double2 d = Ep[0];
+        Ev.m[0].im += b * d.x;
+        Ev.m[4].im += b * d.y;
+        Ev.m[1] = Ev.m[1] + b * ld(Ep + V);
+        Ev.m[2] = Ev.m[2] + b * ld(Ep + 2 * size_t(V));
+        Ev.m[5] = Ev.m[5] + b * ld(Ep + 3 * size_t(V));
+    }
+    if (valid) {
+        st_past(Ep, Ev.m[0].im, Ev.m[4].im);
+        st_past(Ep + V, Ev.m[1].re, Ev.m[1].im);
+        st_past(Ep + 2 * size_t(V), Ev.m[2].re, Ev.m[2].im);
+        st_past(Ep + 3 * size_t(V), Ev.m[5].re, Ev.m[5].im);
+    }
     complete_alg(Ev);
-    st_link(Wout, l, mul(expm_small(Ev), U));
+    const Su3 Wn = mul(expm_small(Ev), U);
+    if constexpr (!CANON) {
+        if (valid) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k)
+                st_past(Wout + size_t(mu * 9 + k) * V + site, Wn.m[k].re, Wn.m[k].im);
+        }
+    } else {
+        __shared__ uint32_t at[kFlowSites];
+        __syncthreads();   // every wave has read the links
+        if (mu == 0) at[lane] = site;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) lds[lane * kSitePitch + mu * 9 + k] = make_double2(Wn.m[k].re, Wn.m[k].im);
+        __syncthreads();
+        const uint32_t n = min(uint32_t(kFlowSites), V - first);
+        for (uint32_t e = threadIdx.x; e < n * 36; e += 4 * kFlowSites) {
+            const uint32_t i = e / 36, k = e - 36 * i;
+            Wout[size_t(at[i]) * 36 + k] = lds[i * kSitePitch + k];
+        }
+    }
+}
+
+// The links between the canonical layout and [mu][entry][site] (TO_SOA or back).
+template <bool TO_SOA>
+__global__ void __launch_bounds__(4 * kFlowSites) k_flow_layout(const double2* in, double2* out, uint32_t V) {
+    __shared__ double2 sh[kFlowSites * kSitePitch];
+    const int lane = threadIdx.x & 63, mu = threadIdx.x >> 6;
+    const uint32_t s0 = blockIdx.x * kFlowSites;
+    const uint32_t n = min(uint32_t(kFlowSites), V - s0);
+    if constexpr (TO_SOA) {
+        for (uint32_t e = threadIdx.x; e < n * 36; e += 4 * kFlowSites)
+            sh[(e / 36) * kSitePitch + e % 36] = in[size_t(s0) * 36 + e];
+        __syncthreads();
+        if (uint32_t(lane) < n)
+#pragma unroll
+            for (int k = 0; k < 9; ++k) out[size_t(mu * 9 + k) * V + s0 + lane] = sh[lane * kSitePitch + mu * 9 + k];
+    } else {
+        if (uint32_t(lane) < n)
+#pragma unroll
+            for (int k = 0; k < 9; ++k) sh[lane * kSitePitch + mu * 9 + k] = in[size_t(mu * 9 + k) * V + s0 + lane];
+        __syncthreads();
+        for (uint32_t e = threadIdx.x; e < n * 36; e += 4 * kFlowSites)
+            out[size_t(s0) * 36 + e] = sh[(e / 36) * kSitePitch + e % 36];
+    }
 }
 
 // sum over the six planes of Re tr U_mu nu(x), block partials in a fixed order
@@ -378,6 +532,9 @@ mdwf_status mdwf_wilson_flow_dev(const mdwf_geometry* geom, double* U_dev, doubl
     const FlowGeo fg{geom->X, geom->Y, geom->Z, geom->T};
     const long nsites = long(fg.X) * fg.Y * fg.Z * fg.T, nlinks = 4 * nsites;
     const size_t bytes = size_t(nlinks) * 9 * sizeof(double2);
+    // the stages address an entry by a 32-bit byte offset; two such fields
+    // are beyond the device's memory anyway
+    if (nsites >= (1L << 28)) return fail(nullptr, MDWF_ERR_OOM, "flow buffer");
     const int nblk_p = int((nsites + kFlowBlock - 1) / kFlowBlock);
     double2 *W2 = nullptr, *E = nullptr;
     double* part = nullptr;
@@ -409,17 +566,38 @@ mdwf_status mdwf_wilson_flow_dev(const mdwf_geometry* geom, double* U_dev, doubl
     }
     if (!s && plaq) s = plaquette_dev(fg, W[0], part, hpart.data(), nsites, nblk_p, st, plaq);
     const double ca[3] = {0.25, 8.0 / 9.0, 0.75}, cb[3] = {0.0, -17.0 / 9.0, -1.0};
-    const unsigned grid = unsigned((nlinks + kFlowBlock - 1) / kFlowBlock);
-    int cur = 0;
-    for (int n = 0; n < nsteps && !s; ++n)
-        for (int i = 0; i < 3 && !s; ++i) {
-            hipLaunchKernelGGL(k_flow_stage, dim3(grid), dim3(kFlowBlock), 0, st, fg, W[cur], W[1 - cur], E,
-                               ca[i] * eps, cb[i], nlinks);
-            s = hip_check(nullptr, hipGetLastError(), "flow kernel");
-            cur = 1 - cur;
-        }
-    // an odd number of stages leaves the result in the scratch buffer
-    if (!s && cur == 1) s = hip_check(nullptr, hipMemcpyAsync(U_dev, W2, bytes, hipMemcpyDeviceToDevice, st), "copy");
+    // stages 0, 2, .. read W2 and write U_dev's memory, in the stage's layout;
+    // the last one writes it in the canonical layout or, an even one, W2
+    const uint32_t V = uint32_t(nsites);
+    const unsigned grid = unsigned((nsites + kFlowSites - 1) / kFlowSites);
+    FlowTrav tv;
+    tv.bz = fg.Z / 8 > 1 ? fg.Z / 8 : 1;
+    tv.xy = FastDiv(uint32_t(fg.X * fg.Y));
+    tv.x = FastDiv(uint32_t(fg.X));
+    tv.plane = FastDiv(uint32_t(fg.X * fg.Y * tv.bz));
+    tv.slab = FastDiv(uint32_t(fg.X * fg.Y * tv.bz) * uint32_t(fg.T));
+    tv.nsites = V;
+    if (!s && nsteps) {
+        hipLaunchKernelGGL(k_flow_layout<true>, dim3(grid), dim3(4 * kFlowSites), 0, st, W[0], W[1], V);
+        s = hip_check(nullptr, hipGetLastError(), "flow layout kernel");
+    }
+    const long nstages = 3L * nsteps;
+    for (long n = 0; n < nstages && !s; ++n) {
+        const double2* in = W[1 - n % 2];
+        double2* out = W[n % 2];
+        const int i = int(n % 3);
+        if (n == nstages - 1 && n % 2 == 0)
+            hipLaunchKernelGGL(k_flow_stage<true>, dim3(grid), dim3(4 * kFlowSites), 0, st, fg, tv, in, out, E,
+                               ca[i] * eps, cb[i]);
+        else
+            hipLaunchKernelGGL(k_flow_stage<false>, dim3(grid), dim3(4 * kFlowSites), 0, st, fg, tv, in, out, E,
+                               ca[i] * eps, cb[i]);
+        s = hip_check(nullptr, hipGetLastError(), "flow kernel");
+    }
+    if (!s && nstages && nstages % 2 == 0) {
+        hipLaunchKernelGGL(k_flow_layout<false>, dim3(grid), dim3(4 * kFlowSites), 0, st, W[1], W[0], V);
+        s = hip_check(nullptr, hipGetLastError(), "flow layout kernel");
+    }
     if (!s && plaq) s = plaquette_dev(fg, W[0], part, hpart.data(), nsites, nblk_p, st, plaq + 1);
     if (!s) s = hip_check(nullptr, hipStreamSynchronize(st), "flow");
     (void)hipFree(W2);
