@@ -127,41 +127,74 @@ __device__ __forceinline__ void g_apply(int mu, bool dag, const cx<double> h[6],
 struct SmearIdx {
     FastDiv fG, fX, fY, fZ;   // G = lanes per site
     uint32_t G;
+    // the one-wave-per-site smearing's order: slabs of by rows, inside one t,
+    // then z, y, x; each XCD sweeps a contiguous part
+    FastDiv slab, slice, plane;   // sites of a slab, of one time slice of it, of one z plane of that
+    uint32_t by;
+    void set_slabs(const SrcGeo& g, uint32_t rows) {
+        by = rows;
+        plane = FastDiv(uint32_t(g.X) * by);
+        slice = FastDiv(uint32_t(g.X) * by * uint32_t(g.Z));
+        slab = FastDiv(uint32_t(g.X) * by * uint32_t(g.Z) * uint32_t(g.T));
+    }
+    __device__ __forceinline__ Site site(const SrcGeo& g, uint32_t pos) const {
+        const uint32_t q = slab.div(pos), r = pos - q * slab.d;
+        const uint32_t t = slice.div(r), r1 = r - t * slice.d;
+        const uint32_t z = plane.div(r1), r2 = r1 - z * plane.d;
+        const uint32_t yy = fX.div(r2);
+        return {int(r2 - yy * uint32_t(g.X)), int(q * by + yy), int(z), int(t)};
+    }
 };
+// the divisor of n nearest below most (or the next one above, if all below are small)
+uint32_t rows(int n, long most) {
+    int lo = 1;
+    for (int d = 1; d <= n; ++d) {
+        if (n % d) continue;
+        if (d <= most) lo = d;
+        else return uint32_t(3L * lo < most ? d : lo);
+    }
+    return uint32_t(lo);
+}
 
 // WAVE: one wavefront per site (nvec <= 16; lanes 4 nvec .. 63 idle), so the
 // site and its links are wave-uniform and the links come by scalar loads.
-// in / out are addressed as base + vector * vs + site * ss (complex units):
-// the canonical layout has vs = 12 * sites, ss = 12; the site-major layout
-// the steps between the first and the last use has vs = 12, ss = 12 * nvec,
-// so a wave's neighbour reads of all vectors are one contiguous run.
+// A field is addressed as base + vector * vs + spin * ps + site * ss + colour * cs
+// (complex units): the canonical layout has vs = 12 sites, ps = 3, ss = 12, cs = 1;
+// between the first step and the last it is [site][colour][vector][spin], so
+// each load of a wave is one contiguous run.
 struct SmearLayout {
-    size_t in_vs, in_ss, out_vs, out_ss;
+    size_t vs, ps, ss, cs;
 };
 
-// The one-site-per-wave path is compiled for four waves per SIMD, so the
-// compiler keeps all its loads in flight (left free, it aims at eight waves
-// and keeps two neighbours' loads in flight; a step was 5 % slower so).
+// What bounds the one-site-per-wave path is the latency of its six links,
+// scalar loads one after the other: with all of them from one cached site a step of
+// twelve vectors at 24^3 x 64 took 170 us less, with its own centre for all
+// neighbours 230 us less.  Five waves a SIMD (96 registers) hide more of it than
+// four, and six spill: 1450, 1360 and 1610 us a step (1583 us before, in the
+// order of the sites and with a vector's colours adjacent).  Links through an
+// LDS broadcast instead measured like the four waves.
 template <bool WAVE>
-__global__ void __launch_bounds__(kSrcBlock) __attribute__((amdgpu_waves_per_eu(WAVE ? 4 : 1, WAVE ? 4 : 8)))
+__global__ void __launch_bounds__(kSrcBlock) __attribute__((amdgpu_waves_per_eu(WAVE ? 5 : 1, WAVE ? 5 : 8)))
 k_gauss_step(const SrcGeo g, const SmearIdx ix, const double2* U, const double2* in, double2* out, double kappa,
-             uint32_t nsites, uint32_t ntot, const SmearLayout lay) {
-    const uint32_t id = blockIdx.x * blockDim.x + threadIdx.x;
+             uint32_t nsites, uint32_t ntot, const SmearLayout li, const SmearLayout lo) {
+    const uint32_t id = uint32_t(xcd_logical_block(blockIdx.x, gridDim.x)) * blockDim.x + threadIdx.x;
     uint32_t i, r;
+    Site st;
     if constexpr (WAVE) {
-        i = uint32_t(__builtin_amdgcn_readfirstlane(int(id >> 6)));
+        const uint32_t pos = uint32_t(__builtin_amdgcn_readfirstlane(int(id >> 6)));
         r = id & 63;
-        if (i >= nsites || r >= ix.G) return;
+        if (pos >= nsites || r >= ix.G) return;
+        st = ix.site(g, pos);
+        i = uint32_t(index_of(g, st.x, st.y, st.z, st.t));
     } else {
         if (id >= ntot) return;
         i = ix.fG.div(id);
         r = id - i * ix.G;
+        const uint32_t q1 = ix.fX.div(i), q2 = ix.fY.div(q1), t = ix.fZ.div(q2);
+        st = {int(i - q1 * g.X), int(q1 - q2 * g.Y), int(q2 - t * g.Z), int(t)};
     }
-    const uint32_t v = r >> 2, sp = r & 3;
-    const uint32_t q1 = ix.fX.div(i), x = i - q1 * g.X;
-    const uint32_t q2 = ix.fY.div(q1), y = q1 - q2 * g.Y;
-    const uint32_t t = ix.fZ.div(q2), z = q2 - t * g.Z;
-    const double2* f = in + size_t(v) * lay.in_vs + sp * 3;
+    const uint32_t v = r >> 2, sp = r & 3, x = st.x, y = st.y, z = st.z;
+    const double2* f = in + size_t(v) * li.vs + sp * li.ps;
     const uint32_t sy = g.X, sz = uint32_t(g.X) * g.Y;
     // neighbours x+mu, x-mu for mu = x, y, z, in that order
     uint32_t xn[6];
@@ -190,23 +223,23 @@ k_gauss_step(const SrcGeo g, const SmearIdx ix, const double2* U, const double2*
 #pragma unroll
         for (int k = 0; k < 6; ++k)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) nv[k][c] = f[size_t(xn[k]) * lay.in_ss + c];
+            for (int c = 0; c < 3; ++c) nv[k][c] = f[size_t(xn[k]) * li.ss + c * li.cs];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) cv[c] = f[size_t(i) * lay.in_ss + c];
+        for (int c = 0; c < 3; ++c) cv[c] = f[size_t(i) * li.ss + c * li.cs];
 #pragma unroll
         for (int k = 0; k < 6; ++k) hop(k, nv[k]);
     } else {
 #pragma unroll 1
         for (int mu = 0; mu < 3; ++mu)
 #pragma unroll
-            for (int dir = 0; dir < 2; ++dir) hop(2 * mu + dir, f + size_t(xn[2 * mu + dir]) * lay.in_ss);
+            for (int dir = 0; dir < 2; ++dir) hop(2 * mu + dir, f + size_t(xn[2 * mu + dir]) * li.ss);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) cv[c] = f[size_t(i) * lay.in_ss + c];
+        for (int c = 0; c < 3; ++c) cv[c] = f[size_t(i) * li.ss + c * li.cs];
     }
-    double2* o = out + size_t(v) * lay.out_vs + size_t(i) * lay.out_ss + sp * 3;
+    double2* o = out + size_t(v) * lo.vs + size_t(i) * lo.ss + sp * lo.ps;
     const double cc = 1.0 - 6.0 * kappa;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) o[c] = make_double2(fma(cc, cv[c].x, kappa * acc[c].re), fma(cc, cv[c].y, kappa * acc[c].im));
+    for (int c = 0; c < 3; ++c) o[c * lo.cs] = make_double2(fma(cc, cv[c].x, kappa * acc[c].re), fma(cc, cv[c].y, kappa * acc[c].im));
 }
 
 // ----------------------------------------------------------- wall source
@@ -575,6 +608,10 @@ mdwf_status mdwf_gauss_smear_dev(const mdwf_geometry* geom, const double* U_dev,
     ix.fY = FastDiv(uint32_t(g.Y));
     ix.fZ = FastDiv(uint32_t(g.Z));
     const bool wave = nvec <= 16;   // one wavefront per site
+    // three planes of a slab (450 KB each) and what is in flight fit an XCD's 4 MB
+    // of L2: with whole z planes of 1.3 MB (twelve vectors at 24^3) a step
+    // fetched 7.1 GB, with slabs 3.6 GB
+    ix.set_slabs(g, rows(g.Y, 450000L / (192L * nvec * g.X)));
     const uint32_t nthr = wave ? uint32_t(nsites * 64) : uint32_t(ntot * 4);
     if (wave && double(nsites) * 64.0 >= double(1u << 31))
         return fail(nullptr, MDWF_ERR_ARG, "lattice too large for one smearing launch");
@@ -584,19 +621,15 @@ mdwf_status mdwf_gauss_smear_dev(const mdwf_geometry* geom, const double* U_dev,
     // the steps between the first and the last keep the fields site-major
     // (all vectors of a site contiguous) when a wavefront holds one site;
     // the last step lands in out, canonical
-    const size_t canon_vs = size_t(nsites) * 12, site_ss = size_t(nvec) * 12;
+    const SmearLayout canon{size_t(nsites) * 12, 3, 12, 1}, inner{4, 1, size_t(nvec) * 12, size_t(nvec) * 4};
     for (int k = 1; k <= niter && !s; ++k) {
         double2* dst = ((niter - k) % 2 == 0) ? out : tmp;
-        SmearLayout lay{canon_vs, 12, canon_vs, 12};
-        if (wave) {
-            if (k > 1) lay.in_vs = 12, lay.in_ss = site_ss;
-            if (k < niter) lay.out_vs = 12, lay.out_ss = site_ss;
+        if (wave)
             hipLaunchKernelGGL(k_gauss_step<true>, dim3(blocks_for(nthr)), dim3(kSrcBlock), 0, st, g, ix, U, src, dst,
-                               kappa, uint32_t(nsites), nthr, lay);
-        } else {
+                               kappa, uint32_t(nsites), nthr, k > 1 ? inner : canon, k < niter ? inner : canon);
+        else
             hipLaunchKernelGGL(k_gauss_step<false>, dim3(blocks_for(nthr)), dim3(kSrcBlock), 0, st, g, ix, U, src,
-                               dst, kappa, uint32_t(nsites), nthr, lay);
-        }
+                               dst, kappa, uint32_t(nsites), nthr, canon, canon);
         s = hip_check(nullptr, hipGetLastError(), "smearing kernel");
         src = dst;
     }
