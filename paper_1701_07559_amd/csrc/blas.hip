@@ -524,28 +524,34 @@ __global__ void __launch_bounds__(256) k_scalars(int op, const double* partials,
                                                  CGScal* sc, double* out_sum) {
     const int rhs = blockIdx.x;
     if (active && !active[rhs]) return;
+    // the chain of a launch bounds this kernel: the scalars are requested before
+    // the sum, the loads of a thread eight at a time, and the last six levels
+    // of the tree stay in one wave
+    const double gamma = sc[rhs].gamma;
     double v = 0.0;
     const double* p = partials + size_t(rhs) * nblk;
+#pragma unroll 8
     for (int k = threadIdx.x; k < nblk; k += 256) v += p[k];
     __shared__ double sh[256];
     sh[threadIdx.x] = v;
     __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
+    if (threadIdx.x >= 64) return;
+    const int l = threadIdx.x;
+    v = (sh[l] + sh[l + 128]) + (sh[l + 64] + sh[l + 192]);
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) v += __shfl_down(v, w, 64);
     if (threadIdx.x != 0) return;
-    const double tot = sh[0];
+    const double tot = v;
     CGScal& c = sc[rhs];
     const bool ok = isfinite(tot);
     switch (op) {
         case SC_ALPHA:
             c.delta = tot;
-            if (ok && tot > 0.0) c.alpha = c.gamma / tot;
+            if (ok && tot > 0.0) c.alpha = gamma / tot;
             else { c.alpha = 0.0; c.bad = 1; }
             break;
         case SC_BETA:
-            if (ok && c.gamma > 0.0) c.beta = tot / c.gamma;
+            if (ok && gamma > 0.0) c.beta = tot / gamma;
             else { c.beta = 0.0; c.bad = 1; }
             c.gamma = tot;
             break;
@@ -559,8 +565,8 @@ __global__ void __launch_bounds__(256) k_scalars(int op, const double* partials,
             break;
         case SC_ALPHA_KEEP:
             c.delta = tot;
-            if (ok && tot > 0.0) c.alpha = c.gamma / tot;
-            else { c.alpha = 0.0; c.bad = 1; }
+            c.alpha = ok && tot > 0.0 ? gamma / tot : 0.0;
+            if (!(ok && tot > 0.0)) c.bad = 1;
             c.alpha_prev = c.alpha;
             break;
         case SC_CLEAR_PREV:
