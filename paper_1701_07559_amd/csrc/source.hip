@@ -472,14 +472,19 @@ __global__ void __launch_bounds__(kSrcBlock) k_corr_partial(const double2* x5, d
     double spp = 0.0, smp = 0.0;
     for (int v = 0; v < nvec; ++v) {
         const double2* x = x5 + size_t(v) * L5 * n + base;
-#pragma unroll 6
+        double2 a[12], c[12];   // a vector's 24 loads in flight: few blocks have to cover them
+#pragma unroll
         for (int k = 0; k < 12; ++k) {
-            const int e = k * kSrcBlock + threadIdx.x;
-            if (e >= cnt) break;
+            const int e = min(k * kSrcBlock + int(threadIdx.x), int(cnt) - 1);
             const bool up = e % 12 < 6;
-            const double2 a = x[(up ? size_t(L5 - 1) * n : 0) + e], c = x[size_t(up ? L5 / 2 - 1 : L5 / 2) * n + e];
-            spp += a.x * a.x + a.y * a.y;
-            smp += c.x * c.x + c.y * c.y;
+            a[k] = x[(up ? size_t(L5 - 1) * n : 0) + e];
+            c[k] = x[size_t(up ? L5 / 2 - 1 : L5 / 2) * n + e];
+        }
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            const bool in = k * kSrcBlock + int(threadIdx.x) < cnt;
+            spp += in ? a[k].x * a[k].x + a[k].y * a[k].y : 0.0;
+            smp += in ? c[k].x * c[k].x + c[k].y * c[k].y : 0.0;
         }
     }
 #pragma unroll
@@ -516,12 +521,12 @@ __global__ void __launch_bounds__(kSrcBlock) k_corr4_partial(const double2* q4, 
     double sum = 0.0;
     for (int v = 0; v < nvec; ++v) {
         const double2* p = q4 + size_t(v) * nsites * 12 + base;
-#pragma unroll 6
-        for (int k = 0; k < 12; ++k) {
-            const int e = k * kSrcBlock + threadIdx.x;
-            if (e >= cnt) break;
-            sum += p[e].x * p[e].x + p[e].y * p[e].y;
-        }
+        double2 a[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) a[k] = p[min(k * kSrcBlock + int(threadIdx.x), int(cnt) - 1)];
+#pragma unroll
+        for (int k = 0; k < 12; ++k)
+            sum += k * kSrcBlock + int(threadIdx.x) < cnt ? a[k].x * a[k].x + a[k].y * a[k].y : 0.0;
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
