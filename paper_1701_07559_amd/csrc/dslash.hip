@@ -13,12 +13,14 @@
 
 namespace mdwf {
 
-// Waves per SIMD the hop kernels are compiled for.  FP16: five (96 VGPRs, no
-// spills); left free, the scheduler takes 130 registers for kernels A / A^+
-// with staged links and they run 20 % slower, at six kernel B of S spills.
-// FP32 and FP64 take what their loads in flight need: held to four and three
-// waves they spill and run 18 % and 7 % slower.
-template <Prec P, int LM> constexpr int hop_waves_per_eu() { return (P == P16 && LM != 3) ? 5 : 1; }
+// Waves per SIMD the hop kernels are compiled for.  FP16 with staged links: five
+// (96 VGPRs, no spills); left free, the scheduler takes 130 registers for
+// kernels A / A^+ and they run 20 % slower, at six kernel B of S spills.  The
+// other link modes of FP16 spill at five where B is applied before the hop
+// (D5 at L5 = 5: 81 us for 53).  FP32 and FP64 take what their loads in
+// flight need: held to four and three waves they spill and run 18 % and 7 %
+// slower.
+template <Prec P, int LM> constexpr int hop_waves_per_eu() { return (P == P16 && LM == 1) ? 5 : 1; }
 
 template <Prec P, int K, int LM>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop_waves_per_eu<P, LM>()))) k_hop(const Geo g, const HopDev a) {
@@ -205,7 +207,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     // ---- epilogue on the hop result
     if constexpr (TR::epi == 1 || TR::epi == 2) {
         // B K5^-1 (or its adjoint) across the L5 lanes
-        five_lanes<TR::epi == 2>(res, ftile, cf.rm, lane, L5, spw);
+        five_lanes<TR::epi == 2, LM != 1>(res, ftile, cf.rm, lane, L5, spw);
     } else if constexpr (TR::epi == 3) {
         if (valid) {   // B^+ = b5 + c5 C^+
             cx<R> cr[12];
@@ -220,7 +222,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     if constexpr (TR::cen == 4 || TR::cen == 5) {
         // lanes past the lattice load site 0 (in bounds; no valid lane reads them)
         Field<P>::load(at_rhs(a.centre, a.stride, rhs), g.Vh, valid ? i * L5 + s : 0, cd);
-        five_lanes<TR::cen == 5>(cd, ftile, cf.rw, lane, L5, spw);
+        five_lanes<TR::cen == 5, LM != 1>(cd, ftile, cf.rw, lane, L5, spw);
     }
 
     double n2 = 0.0;
@@ -288,6 +290,11 @@ template <Prec P, int K>
 static void launch_hop_t(const Geo& g, const GaugeSet& gs, HopLaunch& L, hipStream_t st) {
     int lm = g.link_mode[P];
     if (lm == 1 && 64 / g.L5 > kStageSites) lm = 0;
+    // a launch of few waves waits for the staging instead of gaining by it (same
+    // bits either way): FP32 kernels of 450 workgroups and less ran 10-15 %
+    // slower staged, of 2000 and more faster; FP64, with three times the
+    // link loads to save, gains at every size
+    if (lm == 1 && P == P32 && hop_blocks_per_rhs(g) * L.nrhs <= 1024) lm = 0;
     if (lm == 2 && (P == P64 || g.L5 < link_parts<P>())) lm = 0;
     // matrix cores: FP16, blocks of four slices of one site, no B pre-hop
     if (lm == 3 && (P != P16 || g.L5 % 4 != 0 || HopTraits<K>::preB || !gs.mrow)) lm = 0;

@@ -578,9 +578,45 @@ __device__ __forceinline__ void wave_sync() {
 // 6 i + c runs component c of the wave's site i; a site's lanes are one wave's,
 // so no workgroup barrier is needed.  At L5 = 8 this takes 170 vector
 // instructions for kernel A's 396 of the dense sum.
-template <bool ADJ, typename R>
+// Up to L5 = 6 the chain along the slices takes longer than the L5 - 1 terms
+// themselves: each lane sums its own slice's, with the coefficients
+// B N z^(k-1) (N = 1 / (1 + m_q z^L5) = 1 + w z^L5) of slice s - k, or
+// B w z^(k-1) across the wall.  (FP64 S B^-1 at L5 = 6: the recurrence was 7 %
+// slower than terms, at L5 = 7 the same, at L5 = 12 15 % faster.)
+constexpr int kFiveTerms = 6;
+
+template <bool ADJ, bool TERMS, typename R>
 __device__ __forceinline__ void five_lanes(cx<R> v[12], cx<R>* tile, const double* rec, int lane, int L5, int spw) {
     const R A = R(rec[0]), B = R(rec[1]), z = R(rec[2]), w = R(rec[3]);
+    if (TERMS && L5 <= kFiveTerms) {   // (staged links: L5 >= 8)
+        R zp = R(1);   // z^(L5-1)
+        for (int k = 1; k < L5; ++k) zp *= z;
+        const int s = lane % L5;
+        wave_sync();   // the tile's bytes may hold the wave's links until here
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) tile[c * kFivePitch + lane] = v[6 * half + c];
+            wave_sync();
+            const bool up = (half == 0) != ADJ;   // slice s reads s - k
+            const int past = up ? s : L5 - 1 - s;   // slices before the wall
+            const R own = A + B * w * zp;
+            R cu = B * (R(1) + w * zp * z), cw = B * w;
+#pragma unroll
+            for (int c = 0; c < 6; ++c) v[6 * half + c] = own * v[6 * half + c];
+            for (int k = 1; k < L5; ++k) {
+                // (the lanes past the last whole site stay inside the tile)
+                const int from = min(lane + (up ? -k : k) + (k <= past ? 0 : up ? L5 : -L5), 63);
+                const R f = k <= past ? cu : cw;
+#pragma unroll
+                for (int c = 0; c < 6; ++c) v[6 * half + c] = v[6 * half + c] + f * tile[c * kFivePitch + from];
+                cu *= z;
+                cw *= z;
+            }
+            if (half == 0) wave_sync();
+        }
+        return;
+    }
     wave_sync();   // the tile's bytes may hold the wave's links until here
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
