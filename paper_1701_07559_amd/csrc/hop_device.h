@@ -581,8 +581,8 @@ __device__ __forceinline__ void wave_sync() {
 // Up to L5 = 6 the chain along the slices takes longer than the L5 - 1 terms
 // themselves: each lane sums its own slice's, with the coefficients
 // B N z^(k-1) (N = 1 / (1 + m_q z^L5) = 1 + w z^L5) of slice s - k, or
-// B w z^(k-1) across the wall.  (FP64 S B^-1 at L5 = 6: the recurrence was 7 %
-// slower than terms, at L5 = 7 the same, at L5 = 12 15 % faster.)
+// B w z^(k-1) across the wall.  (Of the operators with these sums the recurrence
+// cost FP64 S B^-1 7 % at L5 = 6 and nothing at L5 = 7.)
 constexpr int kFiveTerms = 6;
 
 template <bool ADJ, bool TERMS, typename R>
