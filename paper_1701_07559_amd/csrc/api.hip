@@ -108,15 +108,30 @@ void* pinned(mdwf_ctx* c, size_t n, mdwf_status* st) {
 
 // K5 = (4 - M5) B + 1 - C = a + b C.  Its inverse on each chirality, using
 // C^L5 = -m_q: K5^-1 = [a (1 + m_q z^L5)]^-1 sum_{k<L5} z^k C^k, z = -b/a.
-// A product (p + q C)(1 - z C)^-1 as the recurrence of five_lanes: the terms
-// A v + B e with A = p, B = q + p z, and the wall factor w.
-static void set_rec(double r[4], double p, double q, double z, double mq, int L5) {
-    double zl = 1.0;
-    for (int k = 0; k < L5; ++k) zl *= z;
-    r[0] = p;
-    r[1] = q + p * z;
-    r[2] = z;
-    r[3] = -mq / (1.0 + mq * zl);
+//
+// (pn + qn C) (pd + qd C)^-1 = (p + q C)(1 - z C)^-1 for five_lanes: A = p,
+// B = q + p z, the wall factor w and the coefficients of C^k, C^0's with
+// the wall's share of C^L5.  Formed in extended precision, so that what the
+// kernels read is rounded once.
+static FiveRec five_rec(long double pn, long double qn, long double pd, long double qd, long double mq, int L5) {
+    const long double p = pn / pd, q = qn / pd, z = -qd / pd;
+    long double zl = 1.0L;   // z^(L5-1)
+    for (int k = 1; k < L5; ++k) zl *= z;
+    const long double n = 1.0L / (1.0L + mq * zl * z), B = q + p * z;
+    FiveRec r;
+    std::memset(&r, 0, sizeof(r));
+    r.A = double(p);
+    r.B = double(B);
+    r.z = double(z);
+    r.w = double(-mq * n);
+    long double zk = n;   // n z^(k-1)
+    for (int k = 0; k < L5 && k < kFiveTerms; ++k) {
+        const long double c = k == 0 ? n * (p - mq * q * zl) : B * zk;
+        r.c[k] = double(c);
+        r.cw[k] = double(-mq * c);
+        if (k) zk *= z;
+    }
+    return r;
 }
 
 RhsCoef make_coef(const mdwf_action& a, double mq) {
@@ -147,8 +162,9 @@ RhsCoef make_coef(const mdwf_action& a, double mq) {
         c.binv[k] = zbk * nb;
         zbk *= zb;
     }
-    set_rec(c.rm, a.b5 / ka, a.c5 / ka, z, mq, L5);   // K5^-1 = (1 - z C)^-1 / ka
-    set_rec(c.rw, ka / a.b5, kb / a.b5, zb, mq, L5);  // B^-1 = (1 - zb C)^-1 / b5
+    const long double m4 = 4.0L - a.M5, la = 1.0L + a.b5 * m4, lb = a.c5 * m4 - 1.0L;   // K5 = la + lb C
+    c.rm = five_rec(a.b5, a.c5, la, lb, mq, L5);
+    c.rw = five_rec(la, lb, a.b5, a.c5, mq, L5);
     return c;
 }
 
@@ -162,7 +178,8 @@ RhsCoef make_coef(const mdwf_action& a, double mq) {
 // the untransformed input.
 RhsCoef make_coef_sym(const mdwf_action& a, double mq) {
     RhsCoef c = make_coef(a, mq);
-    set_rec(c.rm, 1.0 / c.k5[0], 0.0, -c.k5[1] / c.k5[0], mq, a.L5);
+    const long double m4 = 4.0L - a.M5;
+    c.rm = five_rec(1.0L, 0.0L, 1.0L + a.b5 * m4, a.c5 * m4 - 1.0L, mq, a.L5);
     c.k5[0] = 1.0;
     c.k5[1] = 0.0;
     return c;

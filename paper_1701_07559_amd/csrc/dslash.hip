@@ -21,9 +21,18 @@ namespace mdwf {
 // flight need: held to four and three waves they spill and run 18 % and 7 %
 // slower.
 template <Prec P, int LM> constexpr int hop_waves_per_eu() { return (P == P16 && LM == 1) ? 5 : 1; }
+// FP64 kernels with a fifth-dimension operator and no staged links are scheduled
+// for two: at the three that 158 registers allow, fewer loads are in flight and
+// S B^-1 at 24^3 x 32 takes 5 to 7 % longer (L5 = 4 to 7)
+template <int K> constexpr bool hop_five() {
+    return HopTraits<K>::epi == 1 || HopTraits<K>::epi == 2 || HopTraits<K>::cen >= 4;
+}
+template <Prec P, int K, int LM> constexpr int hop_waves_at_most() {
+    return (P == P64 && LM == 0 && hop_five<K>()) ? 2 : 8;
+}
 
 template <Prec P, int K, int LM>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop_waves_per_eu<P, LM>()))) k_hop(const Geo g, const HopDev a) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop_waves_per_eu<P, LM>(), hop_waves_at_most<P, K, LM>()))) k_hop(const Geo g, const HopDev a) {
     using R = typename Real<P>::T;
     using TR = HopTraits<K>;
     const int L5 = g.L5;
@@ -114,7 +123,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     // LDS, per wave: the staged links and, once the hop is done, the tile of
     // five_lanes in the same bytes
     constexpr int kLinkBytes = LM == 1 ? stage_bytes<P>() : 0;
-    constexpr bool kFive = TR::epi == 1 || TR::epi == 2 || TR::cen == 4 || TR::cen == 5;
+    constexpr bool kFive = hop_five<K>();
     constexpr int kFiveBytes = kFive ? (five_bytes<R>() + 15) / 16 * 16 : 0;
     constexpr int kSmem = kLinkBytes > kFiveBytes ? kLinkBytes : kFiveBytes;
     __shared__ __align__(16) unsigned char smem[kWaves][kSmem > 0 ? kSmem : 16];
@@ -207,7 +216,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     // ---- epilogue on the hop result
     if constexpr (TR::epi == 1 || TR::epi == 2) {
         // B K5^-1 (or its adjoint) across the L5 lanes
-        five_lanes<TR::epi == 2, LM != 1>(res, ftile, cf.rm, lane, L5, spw);
+        five_lanes<P, TR::epi == 2, LM != 1>(res, ftile, cf.rm, lane, L5, spw);
     } else if constexpr (TR::epi == 3) {
         if (valid) {   // B^+ = b5 + c5 C^+
             cx<R> cr[12];
@@ -222,7 +231,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     if constexpr (TR::cen == 4 || TR::cen == 5) {
         // lanes past the lattice load site 0 (in bounds; no valid lane reads them)
         Field<P>::load(at_rhs(a.centre, a.stride, rhs), g.Vh, valid ? i * L5 + s : 0, cd);
-        five_lanes<TR::cen == 5, LM != 1>(cd, ftile, cf.rw, lane, L5, spw);
+        five_lanes<P, TR::cen == 5, LM != 1>(cd, ftile, cf.rw, lane, L5, spw);
     }
 
     double n2 = 0.0;

@@ -5,6 +5,8 @@
 // pairs, the per-precision raw neighbour registers and link staging.
 #pragma once
 
+#include <type_traits>
+
 #include "mdwf_internal.h"
 
 namespace mdwf {
@@ -570,27 +572,38 @@ __device__ __forceinline__ void wave_sync() {
 // that chirality (the adjoint: the other way), across the wall with -m_q:
 //   e' = v_s + z e,  out_s = A v_s + B e,  starting from e = w T,
 //   T = sum_s z^(L5-1-s) v_s,  w = -m_q / (1 + m_q z^L5);  rec = (A, B, z, w).
-// |z| < 1 for every accepted action (b5 > c5 >= 0, M5 < 2), so rounding errors
-// do not grow along it.
 // Four operations a slice and component, where the dense L5 x L5 sum takes L5
 // and (in the lanes' own slices) the index arithmetic of every term.  The
 // values go through an LDS tile, the P+ spins and then the P- spins, and lane
 // 6 i + c runs component c of the wave's site i; a site's lanes are one wave's,
 // so no workgroup barrier is needed.  At L5 = 8 this takes 170 vector
 // instructions for kernel A's 396 of the dense sum.
+// Precision: |z| < 1 for every accepted action (b5 > c5 >= 0, M5 < 2), so an
+// error made at one slice decays along the following ones, but one is made at
+// every slice, a rounded z among the causes: in FP32 up to 2.8 times the dense
+// sum's (alternating slices, |z| = 0.53, L5 = 21, m_q = 1).  FP32 fields
+// therefore run it in FP64, whose FMA has the FP32 one's rate, and round the
+// result once: 0.06 to 0.7 times the dense sum's error, for 1 to 3 % of the
+// operator's time.  FP64 fields take coefficients rounded once from extended
+// precision (half the dense sum's error in the median over actions and L5,
+// 2.6 times in the worst case found, both below 1.2e-15); FP16 fields FP32
+// ones, which their storage's rounding hides (error with the dense sums'
+// coefficients to 3e-5 of it).
 // Up to L5 = 6 the chain along the slices takes longer than the L5 - 1 terms
-// themselves: each lane sums its own slice's, with the coefficients
-// B N z^(k-1) (N = 1 / (1 + m_q z^L5) = 1 + w z^L5) of slice s - k, or
-// B w z^(k-1) across the wall.  (Of the operators with these sums the recurrence
-// cost FP64 S B^-1 7 % at L5 = 6 and nothing at L5 = 7.)
-constexpr int kFiveTerms = 6;
-
-template <bool ADJ, bool TERMS, typename R>
-__device__ __forceinline__ void five_lanes(cx<R> v[12], cx<R>* tile, const double* rec, int lane, int L5, int spw) {
-    const R A = R(rec[0]), B = R(rec[1]), z = R(rec[2]), w = R(rec[3]);
+// themselves: each lane sums its own slice's, the coefficients of C^k in rec.c,
+// across the wall those of rec.w.  (Of the operators with these sums the
+// recurrence cost FP64 S B^-1 7 % at L5 = 6 and nothing at L5 = 7.)
+template <Prec P, bool ADJ, bool TERMS>
+__device__ __forceinline__ void five_lanes(cx<typename Real<P>::T> v[12], cx<typename Real<P>::T>* tile,
+                                           const FiveRec& rec, int lane, int L5, int spw) {
+    using R = typename Real<P>::T;
     if (TERMS && L5 <= kFiveTerms) {   // (staged links: L5 >= 8)
-        R zp = R(1);   // z^(L5-1)
-        for (int k = 1; k < L5; ++k) zp *= z;
+        R cu[kFiveTerms], cw[kFiveTerms];
+#pragma unroll
+        for (int k = 0; k < kFiveTerms; ++k) {
+            cu[k] = R(rec.c[k]);
+            cw[k] = R(rec.cw[k]);
+        }
         const int s = lane % L5;
         wave_sync();   // the tile's bytes may hold the wave's links until here
 #pragma unroll
@@ -600,23 +613,24 @@ __device__ __forceinline__ void five_lanes(cx<R> v[12], cx<R>* tile, const doubl
             wave_sync();
             const bool up = (half == 0) != ADJ;   // slice s reads s - k
             const int past = up ? s : L5 - 1 - s;   // slices before the wall
-            const R own = A + B * w * zp;
-            R cu = B * (R(1) + w * zp * z), cw = B * w;
 #pragma unroll
-            for (int c = 0; c < 6; ++c) v[6 * half + c] = own * v[6 * half + c];
-            for (int k = 1; k < L5; ++k) {
+            for (int c = 0; c < 6; ++c) v[6 * half + c] = cu[0] * v[6 * half + c];
+#pragma unroll
+            for (int k = 1; k < kFiveTerms; ++k) {
+                if (k >= L5) break;
                 // (the lanes past the last whole site stay inside the tile)
                 const int from = min(lane + (up ? -k : k) + (k <= past ? 0 : up ? L5 : -L5), 63);
-                const R f = k <= past ? cu : cw;
+                const R f = k <= past ? cu[k] : cw[k];
 #pragma unroll
-                for (int c = 0; c < 6; ++c) v[6 * half + c] = v[6 * half + c] + f * tile[c * kFivePitch + from];
-                cu *= z;
-                cw *= z;
+                for (int c = 0; c < 6; ++c) v[6 * half + c] = axpy(f, tile[c * kFivePitch + from], v[6 * half + c]);
             }
             if (half == 0) wave_sync();
         }
         return;
     }
+    using C = typename std::conditional<P == P32, double, R>::type;
+    const C A = C(rec.A), B = C(rec.B), z = C(rec.z), w = C(rec.w);
+    auto in = [](cx<R> x) { return cx<C>{C(x.re), C(x.im)}; };
     wave_sync();   // the tile's bytes may hold the wave's links until here
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -628,15 +642,15 @@ __device__ __forceinline__ void five_lanes(cx<R> v[12], cx<R>* tile, const doubl
             const int i = int((uint32_t(e) * 10923u) >> 16), c = e - 6 * i;   // e / 6 (e < 384)
             cx<R>* col = tile + c * kFivePitch + i * L5 + (up ? 0 : L5 - 1);
             const int st = up ? 1 : -1;
-            cx<R> T = col[0];
+            cx<C> T = in(col[0]);
 #pragma unroll 4
-            for (int k = 1; k < L5; ++k) T = col[k * st] + z * T;
-            cx<R> f = w * T;
+            for (int k = 1; k < L5; ++k) T = axpy(z, T, in(col[k * st]));
+            cx<C> f = w * T;
 #pragma unroll 4
             for (int k = 0; k < L5; ++k) {
-                const cx<R> x = col[k * st];
-                col[k * st] = A * x + B * f;
-                f = x + z * f;
+                const cx<C> x = in(col[k * st]), o = axpy(A, x, B * f);
+                col[k * st] = {R(o.re), R(o.im)};
+                f = axpy(z, f, x);
             }
         }
         wave_sync();

@@ -25,6 +25,10 @@ template <typename R> __device__ __forceinline__ cx<R> mk(R a, R b) { return {a,
 template <typename R> __device__ __forceinline__ cx<R> operator+(cx<R> a, cx<R> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename R> __device__ __forceinline__ cx<R> operator-(cx<R> a, cx<R> b) { return {a.re - b.re, a.im - b.im}; }
 template <typename R> __device__ __forceinline__ cx<R> operator*(R s, cx<R> a) { return {s * a.re, s * a.im}; }
+// a x + y with one rounding a component
+template <typename R> __device__ __forceinline__ cx<R> axpy(R a, cx<R> x, cx<R> y) {
+    return {fma(a, x.re, y.re), fma(a, x.im, y.im)};
+}
 template <typename R> __device__ __forceinline__ cx<R> timesI(cx<R> a) { return {-a.im, a.re}; }
 template <typename R> __device__ __forceinline__ cx<R> timesMinusI(cx<R> a) { return {a.im, -a.re}; }
 // a * b
@@ -99,17 +103,26 @@ struct Geo {
     int plane_bt[3];    // > 0: bare hops by the plane-staged kernel, this many time planes per workgroup
 };
 
+// (p + q C)(1 - z C)^-1 for the hop kernels (five_lanes): the recurrence's
+// coefficients and, up to kFiveTerms slices, those of C^k in the dense sum,
+// c[k] and across the wall cw[k] = -m_q c[k].  Each is rounded once.
+constexpr int kFiveTerms = 6;
+struct FiveRec {
+    double A, B, z, w;
+    double c[kFiveTerms], cw[kFiveTerms];
+};
+
 // Coefficients of one right-hand side (its mass); all fifth-dimension
-// operators are polynomials in C: sum_k c_k C^k, and those inside the hop
-// kernels recurrences along the slices.
+// operators are polynomials in C: sum_k c_k C^k, and the inverses inside the
+// hop kernels recurrences along the slices.
 struct RhsCoef {
     double mq, b5, c5;
     double k5[2];         // K5 = k5[0] + k5[1] C
     double kinv[kMaxL5];  // K5^-1     = sum_k kinv[k] C^k
     double binv[kMaxL5];  // B^-1      = sum_k binv[k] C^k
-    // The hop kernels' operators as recurrences along the slices (see
-    // five_lanes): B K5^-1 (K5^-1 in the symmetric form's table) and K5 B^-1
-    double rm[4], rw[4];
+    // The hop kernels' operators: B K5^-1 (K5^-1 in the symmetric form's
+    // table) and K5 B^-1
+    FiveRec rm, rw;
 };
 
 // Bytes of a native half field / link segment.
@@ -413,7 +426,7 @@ enum HopKind {
     HOP_SCHUR_B_DAG, // out = K5^+ c - 1/4 B^+ Dslash^+ in
     HOP_PREP,        // out = c + 1/2 Dslash B in
     HOP_BARE_DAG,    // out = Dslash^+ in
-    HOP_SCHUR_B_SYM, // out = c - 1/4 K5^-1 Dslash in (the table's m holds K5^-1)
+    HOP_SCHUR_B_SYM, // out = c - 1/4 K5^-1 Dslash in (the table's rm holds K5^-1)
     // S B^-1 (right preconditioning by B) and its adjoint B^-+ S^+:
     HOP_SCHUR_A_RP,      // out = B K5^-1 Dslash in
     HOP_SCHUR_B_RP,      // out = K5 B^-1 c - 1/4 Dslash in
