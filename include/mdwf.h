@@ -330,7 +330,9 @@ typedef struct {
     int xcd_remap;   /* 1: workgroups renumbered so each XCD walks one contiguous range */
     int nt_store;    /* 1: hop outputs written with non-temporal stores               */
     int link_mode;   /* links: 0 loaded by every lane, 1 staged in LDS (L5 >= 8; in
-                        FP32 for launches of more than 1024 workgroups),
+                        FP32 on lattices of more than 1024 workgroups a
+                        right-hand side for the bare hops, 2500 for D5 and
+                        the Schur right-hand side, 4000 for the Schur forms),
                         2 one 16-byte part per lane, gathered by lane exchange
                         (FP32 / FP16, L5 >= 4 / 2), 3 FP16 SU(3) products on
                         the matrix cores (4x4x4 blocks of four slices of one

@@ -295,19 +295,32 @@ int hop_blocks_per_rhs(const Geo& g) {
     return (g.Vh4 + sites_per_block - 1) / sites_per_block;
 }
 
+// FP32 lattices of few waves wait for the staging instead of gaining by it; with
+// the bits the same, links are staged above this many workgroups a right-hand
+// side.  The line lies on the lattice alone, so that a right-hand side takes the
+// same kernel alone and in any batch.  Staged over unstaged time at one right-hand
+// side (L5 = 8 to 16; at four, each crosses 1 earlier):
+//   bare hops       128 workgroups: 1.12, 432: 1.01, 1080: 0.96, 3000: 0.85
+//   D5 and adjoint  1080: 1.02 and 1.18, 2304: 1.01 and 1.07, 2560: 0.97 and 1.00, 3000: 0.96
+//   S, S B^-1       1080: 1.13 and 1.22, 2304: 1.09 and 1.17, 3840: 1.03 and 1.10,
+//                   4096: 0.96 to 1.04 and 0.95 to 1.09, 6048: 0.98 and 0.96
+// (FP64, with three times the link loads to save, is staged everywhere: below 500
+// workgroups S is up to 3 % slower and S B^-1 4 to 9 % faster.  FP16 too: 0 to 6 %
+// slower below 4000, faster above.)
+template <int K> constexpr int stage_blocks_f32() {
+    return K == HOP_BARE || K == HOP_BARE_DAG ? 1024 : K == HOP_D5 || K == HOP_D5_DAG || K == HOP_PREP ? 2500 : 4000;
+}
+
 template <Prec P, int K>
 static void launch_hop_t(const Geo& g, const GaugeSet& gs, HopLaunch& L, hipStream_t st) {
+    HopDev a;
+    a.nblk = hop_blocks_per_rhs(g);
     int lm = g.link_mode[P];
     if (lm == 1 && 64 / g.L5 > kStageSites) lm = 0;
-    // a launch of few waves waits for the staging instead of gaining by it (same
-    // bits either way): FP32 kernels of 450 workgroups and less ran 10-15 %
-    // slower staged, of 2000 and more faster; FP64, with three times the
-    // link loads to save, gains at every size
-    if (lm == 1 && P == P32 && hop_blocks_per_rhs(g) * L.nrhs <= 1024) lm = 0;
+    if (lm == 1 && P == P32 && a.nblk <= stage_blocks_f32<K>()) lm = 0;
     if (lm == 2 && (P == P64 || g.L5 < link_parts<P>())) lm = 0;
     // matrix cores: FP16, blocks of four slices of one site, no B pre-hop
     if (lm == 3 && (P != P16 || g.L5 % 4 != 0 || HopTraits<K>::preB || !gs.mrow)) lm = 0;
-    HopDev a;
     a.out = L.out;
     a.in = L.in;
     a.centre = L.centre;
@@ -320,7 +333,6 @@ static void launch_hop_t(const Geo& g, const GaugeSet& gs, HopLaunch& L, hipStre
     a.rows_in = gs.mrow ? gs.mrow + size_t(8 + (1 - L.out_parity) * 4) * gs.mrow_bytes : nullptr;
     a.stride = L.stride;
     a.nrhs = L.nrhs;
-    a.nblk = hop_blocks_per_rhs(g);
     a.out_parity = L.out_parity;
     a.coef = L.coef;
     a.active = L.active;
