@@ -330,7 +330,7 @@ typedef struct {
     int xcd_remap;   /* 1: workgroups renumbered so each XCD walks one contiguous range */
     int nt_store;    /* 1: hop outputs written with non-temporal stores               */
     int link_mode;   /* links: 0 loaded by every lane, 1 staged in LDS (L5 >= 8; in
-                        FP32 on lattices of more than 1024 workgroups a
+                        FP32 on lattices of more than 350 workgroups a
                         right-hand side for the bare hops, 2500 for D5 and
                         the Schur right-hand side, 4000 for the Schur forms),
                         2 one 16-byte part per lane, gathered by lane exchange

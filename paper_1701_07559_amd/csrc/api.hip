@@ -110,28 +110,15 @@ void* pinned(mdwf_ctx* c, size_t n, mdwf_status* st) {
 // C^L5 = -m_q: K5^-1 = [a (1 + m_q z^L5)]^-1 sum_{k<L5} z^k C^k, z = -b/a.
 //
 // (pn + qn C) (pd + qd C)^-1 = (p + q C)(1 - z C)^-1 for five_lanes: A = p,
-// B = q + p z, the wall factor w and the coefficients of C^k, C^0's with
-// the wall's share of C^L5.  Formed in extended precision, so that what the
-// kernels read is rounded once.
+// B = q + p z, the wall factor w and the coefficients of C^0 and C^1, the first
+// with the wall's share of C^L5.  Formed in extended precision, so that what
+// the kernels read is rounded once.
 static FiveRec five_rec(long double pn, long double qn, long double pd, long double qd, long double mq, int L5) {
     const long double p = pn / pd, q = qn / pd, z = -qd / pd;
     long double zl = 1.0L;   // z^(L5-1)
     for (int k = 1; k < L5; ++k) zl *= z;
     const long double n = 1.0L / (1.0L + mq * zl * z), B = q + p * z;
-    FiveRec r;
-    std::memset(&r, 0, sizeof(r));
-    r.A = double(p);
-    r.B = double(B);
-    r.z = double(z);
-    r.w = double(-mq * n);
-    long double zk = n;   // n z^(k-1)
-    for (int k = 0; k < L5 && k < kFiveTerms; ++k) {
-        const long double c = k == 0 ? n * (p - mq * q * zl) : B * zk;
-        r.c[k] = double(c);
-        r.cw[k] = double(-mq * c);
-        if (k) zk *= z;
-    }
-    return r;
+    return {double(p), double(B), double(z), double(-mq * n), double(n * (p - mq * q * zl)), double(n * B)};
 }
 
 RhsCoef make_coef(const mdwf_action& a, double mq) {

@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     // ---- epilogue on the hop result
     if constexpr (TR::epi == 1 || TR::epi == 2) {
         // B K5^-1 (or its adjoint) across the L5 lanes
-        five_lanes<P, TR::epi == 2, LM != 1>(res, ftile, cf.rm, lane, L5, spw);
+        five_lanes<P, TR::epi == 2, LM != 1>(res, ftile, cf.rm, cf.mq, lane, L5, spw);
     } else if constexpr (TR::epi == 3) {
         if (valid) {   // B^+ = b5 + c5 C^+
             cx<R> cr[12];
@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     if constexpr (TR::cen == 4 || TR::cen == 5) {
         // lanes past the lattice load site 0 (in bounds; no valid lane reads them)
         Field<P>::load(at_rhs(a.centre, a.stride, rhs), g.Vh, valid ? i * L5 + s : 0, cd);
-        five_lanes<P, TR::cen == 5, LM != 1>(cd, ftile, cf.rw, lane, L5, spw);
+        five_lanes<P, TR::cen == 5, LM != 1>(cd, ftile, cf.rw, cf.mq, lane, L5, spw);
     }
 
     double n2 = 0.0;
@@ -300,7 +300,8 @@ int hop_blocks_per_rhs(const Geo& g) {
 // side.  The line lies on the lattice alone, so that a right-hand side takes the
 // same kernel alone and in any batch.  Staged over unstaged time at one right-hand
 // side (L5 = 8 to 16; at four, each crosses 1 earlier):
-//   bare hops       128 workgroups: 1.12, 432: 1.01, 1080: 0.96, 3000: 0.85
+//   bare hops       128 workgroups: 1.12, 216: 1.09, 432: 1.01, 1080: 0.96, 3000: 0.85
+//                   (four right-hand sides: 1.01, 0.96, 0.93, 0.88, 0.91)
 //   D5 and adjoint  1080: 1.02 and 1.18, 2304: 1.01 and 1.07, 2560: 0.97 and 1.00, 3000: 0.96
 //   S, S B^-1       1080: 1.13 and 1.22, 2304: 1.09 and 1.17, 3840: 1.03 and 1.10,
 //                   4096: 0.96 to 1.04 and 0.95 to 1.09, 6048: 0.98 and 0.96
@@ -308,7 +309,7 @@ int hop_blocks_per_rhs(const Geo& g) {
 // workgroups S is up to 3 % slower and S B^-1 4 to 9 % faster.  FP16 too: 0 to 6 %
 // slower below 4000, faster above.)
 template <int K> constexpr int stage_blocks_f32() {
-    return K == HOP_BARE || K == HOP_BARE_DAG ? 1024 : K == HOP_D5 || K == HOP_D5_DAG || K == HOP_PREP ? 2500 : 4000;
+    return K == HOP_BARE || K == HOP_BARE_DAG ? 350 : K == HOP_D5 || K == HOP_D5_DAG || K == HOP_PREP ? 2500 : 4000;
 }
 
 template <Prec P, int K>

@@ -590,19 +590,22 @@ __device__ __forceinline__ void wave_sync() {
 // ones, which their storage's rounding hides (error with the dense sums'
 // coefficients to 3e-5 of it).
 // Up to L5 = 6 the chain along the slices takes longer than the L5 - 1 terms
-// themselves: each lane sums its own slice's, the coefficients of C^k in rec.c,
-// across the wall those of rec.w.  (Of the operators with these sums the
+// themselves: each lane sums its own slice's, with coefficients formed in FP64
+// and rounded once, those across the wall times -m_q.  (Of the operators with these sums the
 // recurrence cost FP64 S B^-1 7 % at L5 = 6 and nothing at L5 = 7.)
 template <Prec P, bool ADJ, bool TERMS>
 __device__ __forceinline__ void five_lanes(cx<typename Real<P>::T> v[12], cx<typename Real<P>::T>* tile,
-                                           const FiveRec& rec, int lane, int L5, int spw) {
+                                           const FiveRec& rec, double mq, int lane, int L5, int spw) {
     using R = typename Real<P>::T;
     if (TERMS && L5 <= kFiveTerms) {   // (staged links: L5 >= 8)
         R cu[kFiveTerms], cw[kFiveTerms];
+        cu[0] = R(rec.c0);
+        double ck = rec.c1;
 #pragma unroll
-        for (int k = 0; k < kFiveTerms; ++k) {
-            cu[k] = R(rec.c[k]);
-            cw[k] = R(rec.cw[k]);
+        for (int k = 1; k < kFiveTerms; ++k) {
+            cu[k] = R(ck);
+            cw[k] = R(-mq * ck);
+            ck *= rec.z;
         }
         const int s = lane % L5;
         wave_sync();   // the tile's bytes may hold the wave's links until here

@@ -104,12 +104,11 @@ struct Geo {
 };
 
 // (p + q C)(1 - z C)^-1 for the hop kernels (five_lanes): the recurrence's
-// coefficients and, up to kFiveTerms slices, those of C^k in the dense sum,
-// c[k] and across the wall cw[k] = -m_q c[k].  Each is rounded once.
+// coefficients and, for the dense sum up to kFiveTerms slices, those of C^0 and
+// C^1 (z times the one before from there on).  Each is rounded once.
 constexpr int kFiveTerms = 6;
 struct FiveRec {
-    double A, B, z, w;
-    double c[kFiveTerms], cw[kFiveTerms];
+    double A, B, z, w, c0, c1;
 };
 
 // Coefficients of one right-hand side (its mass); all fifth-dimension
