@@ -373,7 +373,9 @@ mdwf_status mdwf_autotune(mdwf_ctx *ctx, mdwf_launch_tune *out);
  * bad options. */
 mdwf_status mdwf_autotune_solve(mdwf_ctx *ctx, const mdwf_solver_opts *opts, int nrhs, mdwf_launch_tune *out);
 
-/* Current launch shape of precision `prec` (defaults before autotuning). */
+/* Current launch shape of precision `prec`: the default for the lattice and,
+ * once the action is set, its L5, until mdwf_set_tune or an autotuning installs
+ * another, which later actions keep. */
 mdwf_status mdwf_get_tune(const mdwf_ctx *ctx, mdwf_prec prec, mdwf_launch_tune *out);
 
 /* Install a launch shape for precision `prec` (e.g. one mdwf_autotune chose

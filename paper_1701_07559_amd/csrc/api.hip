@@ -1,4 +1,5 @@
 // C ABI of libmdwf: context, gauge upload, action, operator application.
+#include <algorithm>
 #include <array>
 #include <cmath>
 #include <cstdio>
@@ -229,6 +230,68 @@ void set_tune(Geo& g, Prec p, const mdwf_launch_tune& t) {
     g.plane_bt[p] = (t.plane_bt > 0 && g.T % t.plane_bt == 0) ? t.plane_bt : 0;
 }
 
+// The launch options of the environment, MDWF_TILE ("bx,by,bz,bt") and the
+// others; -1 (tile 0) where a variable is not set.
+static mdwf_launch_tune environment_tune(const Geo& g) {
+    mdwf_launch_tune t{{0, 0, 0, 0}, -1, -1, -1, -1, 0.0, -1};
+    if (const char* e = std::getenv("MDWF_TILE")) {
+        int b[4];
+        if (std::sscanf(e, "%d,%d,%d,%d", &b[0], &b[1], &b[2], &b[3]) == 4 && tile_fits(g, b))
+            std::copy(b, b + 4, t.tile);
+    }
+    if (const char* e = std::getenv("MDWF_XCD_REMAP")) t.xcd_remap = std::atoi(e) != 0;
+    if (const char* e = std::getenv("MDWF_NT_STORE")) t.nt_store = std::atoi(e) != 0;
+    if (const char* e = std::getenv("MDWF_LINK_MODE")) t.link_mode = std::max(0, std::atoi(e));
+    if (const char* e = std::getenv("MDWF_RHS_GROUP")) t.rhs_group = std::max(0, std::atoi(e));
+    if (const char* e = std::getenv("MDWF_PLANE_BT")) t.plane_bt = std::max(0, std::atoi(e));
+    return t;
+}
+
+// Default launch shape of a lattice and, once the action is set, L5
+// (mdwf_autotune times others against it; what the environment set when the
+// context was made, e, overrides it):
+//  - eight spatial columns marched along t, one per XCD, so that none cuts
+//    a tile and each one's time planes stay in its L2 (FP64 S at 24^3 x 64,
+//    L5 = 8: 1174 us for 1259 us with six z-blocks; FP32 hop 254 for 271).
+//    Z-blocks of 4 (or 2) planes with t inside for columns of fewer than 192
+//    sites a plane (three FP32 RHS at 12^3 x 24: 56.0 ms a solve for 57.8 ms),
+//    for extents they don't divide, and where a column's rows are 8 KB of
+//    every 16 KB of a field whose element blocks lie a multiple of 4 MB
+//    apart: there the columns collide in the caches (FP64 S at L5 = 8:
+//    16^4 88 us for 124, 16^3 x 32 178 for 223, 16^3 x 48 268 for 293,
+//    16^3 x 64 358 for 379; half or twice the run, or blocks of 2 MB
+//    multiples, e.g. 16^3 x 24 or L5 = 10 and 12, within 2 %; FP32 up to 5 %
+//    either way, FP16 the same)
+//  - links staged in LDS (L5 >= 8; FP64 S 1383 -> 1284 us and FP32 hop
+//    316 -> 277 us at 24^3 x 64; small FP32 lattices: see launch_hop)
+//  - one right-hand side after the other: a tile's together share its links
+//    but evict each other's neighbours from L2 (FP16, twelve at
+//    24^3 x 32, L5 = 10: 5068 us for 5660 us; six FP64 at 16^3 x 32, 2049 for 2287)
+//  - FP16 results stored past L2, which the next kernel's first reads don't
+//    find there either way (twelve at 24^3 x 64: 7550 us for 7730 us; FP32 and FP64
+//    measure the same)
+static mdwf_launch_tune default_tune(const Geo& g, Prec p, const mdwf_launch_tune& e) {
+    mdwf_launch_tune t{{g.Xh, g.Y, (g.Z % 4 == 0) ? 4 : 2, 1}, 1, p == P16, 1, 1, 0.0, 0};
+    const bool collide = long(g.Xh) * (g.Y / 2) * g.L5 * 16 == 8192 && long(g.Vh) * 16 % (4L << 20) == 0;
+    if (g.Z % 4 == 0 && g.Xh * (g.Y / 2) * (g.Z / 4) >= 192 && !collide) {
+        t.tile[1] = g.Y / 2;
+        t.tile[2] = g.Z / 4;
+        t.tile[3] = 2;
+    }
+    if (e.tile[0]) std::copy(e.tile, e.tile + 4, t.tile);
+    if (e.xcd_remap >= 0) t.xcd_remap = e.xcd_remap;
+    if (e.nt_store >= 0) t.nt_store = e.nt_store;
+    if (e.link_mode >= 0) t.link_mode = e.link_mode;
+    if (e.rhs_group >= 0) t.rhs_group = e.rhs_group;
+    if (e.plane_bt >= 0) t.plane_bt = e.plane_bt;
+    return t;
+}
+// for the precisions whose shape nothing else has chosen
+static void install_default_tunes(mdwf_ctx* c) {
+    for (int p = 0; p < 3; ++p)
+        if (!c->tune_set[p]) set_tune(c->geo, Prec(p), default_tune(c->geo, Prec(p), c->env_tune));
+}
+
 void release_solver_buffers(mdwf_ctx* c) {
     (void)hipSetDevice(c->device);
     if (c->stream) (void)hipStreamSynchronize(c->stream);
@@ -442,43 +505,8 @@ mdwf_status mdwf_create(const mdwf_geometry* geom, int hip_device, void* hip_str
     g.fXh = FastDiv(uint32_t(g.Xh));
     g.fY = FastDiv(uint32_t(g.Y));
     g.fZ = FastDiv(uint32_t(g.Z));
-    // default launch shape (mdwf_autotune refines it per precision; the
-    // MDWF_TILE ("bx,by,bz,bt"), MDWF_XCD_REMAP, MDWF_NT_STORE, MDWF_LINK_MODE
-    // and MDWF_RHS_GROUP variables override it):
-    //  - eight spatial columns marched along t, one per XCD, so that none cuts
-    //    a tile and each one's time planes stay in its L2 (FP64 S at 24^3 x 64,
-    //    L5 = 8: 1174 us for 1259 us with six z-blocks; FP32 hop 254 for 271).
-    //    Columns of fewer than 192 sites a plane, or extents they don't divide,
-    //    keep z-blocks of 4 (or 2) planes with t inside (three FP32 RHS at
-    //    12^3 x 24: 56.0 ms a solve for 57.8 ms)
-    //  - links staged in LDS (L5 >= 8; against every lane loading them: FP32
-    //    hop 316 -> 277 us, FP64 S 1383 -> 1284 us at 24^3 x 64, no shape slower)
-    //  - one right-hand side after the other: a tile's together share its links
-    //    but evict each other's neighbours from L2 (FP16, twelve at
-    //    24^3 x 32, L5 = 10: 5068 us for 5660 us; six FP64 at 16^3 x 32, 2049 for 2287)
-    //  - FP16 results stored past L2, which the next kernel's first reads don't
-    //    find there either way (twelve at 24^3 x 64: 7550 us for 7730 us; FP32 and FP64
-    //    measure the same)
-    mdwf_launch_tune t0{{g.Xh, g.Y, (g.Z % 4 == 0) ? 4 : 2, 1}, 1, 0, 1, 1, 0.0, 0};
-    if (g.Z % 4 == 0 && g.Xh * (g.Y / 2) * (g.Z / 4) >= 192) {
-        t0.tile[1] = g.Y / 2;
-        t0.tile[2] = g.Z / 4;
-        t0.tile[3] = 2;
-    }
-    if (const char* e = std::getenv("MDWF_TILE")) {
-        int b[4];
-        if (std::sscanf(e, "%d,%d,%d,%d", &b[0], &b[1], &b[2], &b[3]) == 4 && tile_fits(g, b))
-            for (int k = 0; k < 4; ++k) t0.tile[k] = b[k];
-    }
-    if (const char* e = std::getenv("MDWF_XCD_REMAP")) t0.xcd_remap = std::atoi(e) != 0;
-    const char* nt = std::getenv("MDWF_NT_STORE");
-    if (const char* e = std::getenv("MDWF_LINK_MODE")) t0.link_mode = std::atoi(e);
-    if (const char* e = std::getenv("MDWF_RHS_GROUP")) t0.rhs_group = std::atoi(e);
-    if (const char* e = std::getenv("MDWF_PLANE_BT")) t0.plane_bt = std::atoi(e);
-    for (int p = 0; p < 3; ++p) {
-        t0.nt_store = nt ? std::atoi(nt) != 0 : p == P16;
-        set_tune(g, Prec(p), t0);
-    }
+    c->env_tune = environment_tune(g);
+    install_default_tunes(c);
     scratch_init(hip_device);   // the device address of this device's static scratch
     if (hipMalloc(&c->d_coef1, 2 * sizeof(RhsCoef)) != hipSuccess) {
         (void)hipGetLastError();
@@ -598,6 +626,7 @@ mdwf_status mdwf_set_action(mdwf_ctx* c, const mdwf_action* a) {
     c->act = *a;
     c->geo.L5 = a->L5;
     c->geo.Vh = c->geo.Vh4 * a->L5;
+    install_default_tunes(c);
     const RhsCoef cf[2] = {make_coef(*a, a->mq), make_coef_sym(*a, a->mq)};
     s = hip_check(c, hipMemcpyAsync(c->d_coef1, cf, sizeof(cf), hipMemcpyHostToDevice, c->stream),
                   "coefficient upload");
@@ -765,6 +794,7 @@ mdwf_status mdwf_set_tune(mdwf_ctx* c, mdwf_prec prec, const mdwf_launch_tune* t
     if (t->plane_bt < 0 || (t->plane_bt > 0 && c->geo.T % t->plane_bt))
         return fail(c, MDWF_ERR_ARG, "plane_bt must divide T");
     set_tune(c->geo, Prec(prec), *t);   // enqueued launches took the old shape by value
+    c->tune_set[prec] = true;
     c->tuned_us[prec] = t->us;
     return MDWF_OK;
 }
@@ -912,6 +942,7 @@ mdwf_status tune_precision(mdwf_ctx* c, Prec p, int form, int nrhs, bool with_da
         set_tune(g, p, best);
     }
     c->tuned_us[p] = best.us;
+    c->tune_set[p] = true;
     if (out) *out = best;
     return MDWF_OK;
 }

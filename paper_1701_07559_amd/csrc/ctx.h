@@ -35,6 +35,10 @@ struct mdwf_ctx {
     size_t h_pin_n = 0;
     // autotuned time of one Schur application per precision (0 = not tuned)
     double tuned_us[3] = {0.0, 0.0, 0.0};
+    // launch shape per precision chosen by the caller or the autotuner: kept
+    // when the action changes, where the default follows L5
+    bool tune_set[3] = {false, false, false};
+    mdwf_launch_tune env_tune{};   // launch options of the environment at creation
 };
 
 namespace mdwf {

@@ -1,0 +1,56 @@
+"""Default launch shape per lattice and L5: spatial columns, z-blocks where a
+column's rows are 8 KB of every 16 KB of a field whose element blocks lie a
+multiple of 4 MB apart.  It follows the action until the caller installs a
+shape, which later actions keep; results don't depend on it."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1701_07559_amd import inputs as I
+
+import test_gpu_parity as TP
+
+pytestmark = pytest.mark.gpu
+M = TP.M
+
+Z, C = "z-blocks", "columns"
+
+
+def shape(M, dims, L5):
+    ctx = M.mdwf_create(dims)
+    try:
+        M.mdwf_set_action(ctx, 1.3, 1.5, 0.5, 0.05, L5)
+        return [M.mdwf_get_tune(ctx, p) for p in range(3)]
+    finally:
+        M.mdwf_destroy(ctx)
+
+
+@pytest.mark.parametrize("dims,L5,kind", [
+    ((16, 16, 16, 16), 8, Z), ((16, 16, 16, 32), 8, Z), ((8, 32, 32, 8), 8, Z), ((16, 32, 16, 16), 4, Z),
+    ((16, 16, 16, 48), 8, Z), ((16, 16, 16, 16), 7, C), ((16, 16, 16, 16), 10, C), ((16, 16, 16, 16), 16, C),
+    ((16, 16, 16, 24), 8, C), ((16, 32, 16, 16), 8, C), ((24, 24, 24, 8), 8, C), ((12, 12, 12, 8), 8, Z),
+    ((18, 18, 18, 8), 8, Z)], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_default_tile(M, dims, L5, kind):
+    X, Y, ZZ, T = dims
+    want = [X // 2, Y // 2, ZZ // 4, 2] if kind == C else [X // 2, Y, 4 if ZZ % 4 == 0 else 2, 1]
+    assert all(t["tile"] == want for t in shape(M, dims, L5))
+
+
+def test_the_shape_follows_the_action_until_one_is_installed(M):
+    dims = (16, 16, 16, 16)
+    act = oracle.Action(dims, 8, M5=1.3, b5=1.5, c5=0.5, mq=0.05)
+    ctx = TP.make_ctx(M, act, I.random_links(dims, 0.3, 61))
+    psi = I.gaussian_source(dims, 8, 62).reshape(8, -1, 4, 3)[:, ::2].copy()
+    try:
+        z, out = M.mdwf_get_tune(ctx, 0)["tile"], [np.zeros_like(psi) for _ in range(2)]
+        M.mdwf_apply(ctx, M.MDWF_OP_SCHUR, 0, psi, out[0])
+        M.mdwf_set_action(ctx, 1.3, 1.5, 0.5, 0.05, 10)
+        col = M.mdwf_get_tune(ctx, 0)
+        assert z == [8, 16, 4, 1] and col["tile"] == [8, 8, 4, 2]
+        M.mdwf_set_tune(ctx, 0, col)
+        M.mdwf_set_action(ctx, 1.3, 1.5, 0.5, 0.05, 8)
+        assert [M.mdwf_get_tune(ctx, p)["tile"] for p in range(3)] == [col["tile"], z, z]
+        M.mdwf_apply(ctx, M.MDWF_OP_SCHUR, 0, psi, out[1])
+        assert out[0].any() and np.array_equal(out[0], out[1])
+    finally:
+        M.mdwf_destroy(ctx)
