@@ -1,6 +1,7 @@
 """Default launch shape per lattice and L5: spatial columns, z-blocks where a
 column's rows are 8 KB of every 16 KB of a field whose element blocks lie a
-multiple of 4 MB apart.  It follows the action until the caller installs a
+multiple of 4 MB apart; right-hand sides one after the other, or where links of
+short fifth dimensions weigh more than a field, together.  It follows the action until the caller installs a
 shape, which later actions keep; results don't depend on it."""
 import numpy as np
 import pytest
@@ -34,6 +35,11 @@ def test_default_tile(M, dims, L5, kind):
     X, Y, ZZ, T = dims
     want = [X // 2, Y // 2, ZZ // 4, 2] if kind == C else [X // 2, Y, 4 if ZZ % 4 == 0 else 2, 1]
     assert all(t["tile"] == want for t in shape(M, dims, L5))
+
+
+@pytest.mark.parametrize("L5,groups", [(4, [0, 2, 2]), (5, [0, 2, 2]), (6, [1, 1, 1]), (8, [1, 1, 1])])
+def test_default_rhs_group(M, L5, groups):
+    assert [t["rhs_group"] for t in shape(M, (12, 12, 12, 8), L5)] == groups
 
 
 def test_the_shape_follows_the_action_until_one_is_installed(M):
