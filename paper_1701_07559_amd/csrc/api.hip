@@ -293,6 +293,40 @@ static mdwf_launch_tune default_tune(const Geo& g, Prec p, const mdwf_launch_tun
     if (e.plane_bt >= 0) t.plane_bt = e.plane_bt;
     return t;
 }
+// Shapes every tuning of precision p times first: the installed one and the
+// lattice's default, so that its choice is never slower than either.
+std::vector<mdwf_launch_tune> tune_starts(const Geo& g, Prec p, const mdwf_launch_tune& env) {
+    mdwf_launch_tune t{{0, 0, 0, 0}, g.xcd_remap[p], g.nt_store[p], g.link_mode[p], g.rhs_group[p], 0.0, g.plane_bt[p]};
+    std::copy(g.trav[p].b, g.trav[p].b + 4, t.tile);
+    mdwf_launch_tune d = default_tune(g, p, env);
+    d.plane_bt = t.plane_bt;   // the bare hop's, tuned by itself
+    std::vector<mdwf_launch_tune> v{t};
+    if (!std::equal(d.tile, d.tile + 4, t.tile) || d.xcd_remap != t.xcd_remap || d.nt_store != t.nt_store ||
+        d.link_mode != t.link_mode || d.rhs_group != t.rhs_group)
+        v.push_back(d);
+    return v;
+}
+// Traversal tiles a tuning tries from there: z-blocks, the eight spatial columns
+// at several depths in t, and compact 4D tiles.
+std::vector<std::array<int, 4>> tune_tiles(const Geo& g) {
+    std::vector<std::array<int, 4>> tiles;
+    auto add = [&](int bx, int by, int bz, int bt) {
+        const std::array<int, 4> b{bx, by, bz, bt};
+        if (tile_fits(g, b.data()) && std::find(tiles.begin(), tiles.end(), b) == tiles.end()) tiles.push_back(b);
+    };
+    for (int v : {1, 2, 4, 8, 16}) add(g.Xh, g.Y, v, 1);
+    add(g.Xh, g.Y, g.Z, 1);
+    if (g.Z % 4 == 0)
+        for (int bt : {1, 2, 4}) add(g.Xh, g.Y / 2, g.Z / 4, bt);
+    for (int bx : {g.Xh, g.Xh / 2})
+        for (int by : {4, 6, 8, 12, g.Y})
+            for (int bz : {2, 4, 6, 8})
+                for (int bt : {1, 2, 4}) {
+                    const long vol = long(bx) * by * bz * bt;
+                    if (vol >= 384 && vol <= 6912 && (by < g.Y || bt > 1)) add(bx, by, bz, bt);
+                }
+    return tiles;
+}
 // for the precisions whose shape nothing else has chosen
 static void install_default_tunes(mdwf_ctx* c) {
     for (int p = 0; p < 3; ++p)
@@ -812,8 +846,8 @@ namespace {
 
 // Coordinate-descent tuning of precision p's launch shape on the CG operator
 // of Schur form `form` with nrhs RHS per launch (its adjoint too when
-// `with_dag`): traversal tile (z-blocks and compact 4D tiles), link mode,
-// non-temporal stores and workgroup numbering, then (nrhs > 1) the RHS
+// `with_dag`), from the installed and the default shape: traversal tile, link
+// mode, non-temporal stores and workgroup numbering, then (nrhs > 1) the RHS
 // grouping.  Each candidate: 2 warm-up applications, the mean of 5 timed.
 // For one RHS without the adjoint (the operator tuning), FP32 and FP16 also
 // choose the kernel of the bare hop (lane-per-site or plane-staged).
@@ -822,23 +856,6 @@ mdwf_status tune_precision(mdwf_ctx* c, Prec p, int form, int nrhs, bool with_da
     Geo& g = c->geo;
     hipStream_t st = c->stream;
     mdwf_status s = MDWF_OK;
-    std::vector<std::array<int, 4>> tiles;
-    auto add_tile = [&](int bx, int by, int bz, int bt) {
-        const int b4[4] = {bx, by, bz, bt};
-        if (!tile_fits(g, b4)) return;
-        for (const auto& t : tiles)
-            if (t[0] == bx && t[1] == by && t[2] == bz && t[3] == bt) return;
-        tiles.push_back({bx, by, bz, bt});
-    };
-    for (int v : {1, 2, 4, 8, 16}) add_tile(g.Xh, g.Y, v, 1);
-    add_tile(g.Xh, g.Y, g.Z, 1);
-    for (int bx : {g.Xh, g.Xh / 2})
-        for (int by : {4, 6, 8, 12, g.Y})
-            for (int bz : {2, 4, 6, 8})
-                for (int bt : {1, 2, 4}) {
-                    const long vol = long(bx) * by * bz * bt;
-                    if (vol >= 384 && vol <= 6912 && (by < g.Y || bt > 1)) add_tile(bx, by, bz, bt);
-                }
     const size_t hb = half_field_bytes(p, g.Vh);
     // scratch: nrhs even inputs (packed from the canonical pattern), outputs
     // of the operator and of its adjoint (the input is never overwritten, so
@@ -879,20 +896,24 @@ mdwf_status tune_precision(mdwf_ctx* c, Prec p, int form, int nrhs, bool with_da
         tn.us = 1e3 * ms / reps;
         return tn;
     };
-    mdwf_launch_tune best{};
-    for (int k = 0; k < 4; ++k) best.tile[k] = g.trav[p].b[k];
-    best.xcd_remap = 1;
-    best.rhs_group = g.rhs_group[p];
-    best.plane_bt = g.plane_bt[p];   // bare hops only: kept unless chosen below
+    const auto starts = tune_starts(g, p, c->env_tune);
+    mdwf_launch_tune best = timed(starts[0]);   // (clocks and caches warm)
     best.us = 1e30;
-    for (const auto& tl : tiles) {
+    for (const auto& start : starts) {
+        const mdwf_launch_tune tn = s ? start : timed(start);
+        if (s) return s;
+        if (tn.us < best.us) best = tn;
+    }
+    for (const auto& tl : tune_tiles(g)) {
         mdwf_launch_tune tn = best;
-        for (int k = 0; k < 4; ++k) tn.tile[k] = tl[k];
+        std::copy(tl.begin(), tl.end(), tn.tile);
         tn = timed(tn);
         if (s) return s;
         if (tn.us < best.us) best = tn;
     }
-    for (int lm : {1, 2, 3}) {
+    const int lm0 = best.link_mode;
+    for (int lm : {0, 1, 2, 3}) {
+        if (lm == lm0) continue;
         if (lm == 1 && 64 / g.L5 > 8) continue;
         if (lm == 2 && (p == P64 || g.L5 < (p == P32 ? 4 : 2))) continue;
         if (lm == 3 && (p != P16 || g.L5 % 4 != 0)) continue;
@@ -919,6 +940,13 @@ mdwf_status tune_precision(mdwf_ctx* c, Prec p, int form, int nrhs, bool with_da
             if (s) return s;
             if (tn.us < best.us) best = tn;
         }
+    // the choice once more against the shapes it started from
+    best = timed(best);
+    for (const auto& start : starts) {
+        const mdwf_launch_tune tn = s ? start : timed(start);
+        if (s) return s;
+        if (tn.us < best.us) best = tn;
+    }
     set_tune(g, p, best);
     // The bare hops (MDWF_OP_HOP_*) can also run plane-staged: keep the
     // plane run that times fastest on one bare hop (0 = the lane kernel).

@@ -1,6 +1,7 @@
 // Context object behind the opaque mdwf_ctx handle.
 #pragma once
 
+#include <array>
 #include <map>
 #include <string>
 #include <vector>
@@ -60,6 +61,10 @@ void schur_launch(const Geo& g, const GaugeSet& gs, Prec p, int form, bool dag, 
 
 // Install a launch shape for one precision in the geometry.
 void set_tune(Geo& g, Prec p, const mdwf_launch_tune& t);
+// What a tuning of precision p times: whole shapes first (env: the launch
+// options of the environment, -1 and tile 0 where none), then tiles.
+std::vector<mdwf_launch_tune> tune_starts(const Geo& g, Prec p, const mdwf_launch_tune& env);
+std::vector<std::array<int, 4>> tune_tiles(const Geo& g);
 
 // Native-layout operator application on `nrhs` right-hand sides stored at
 // byte stride `stride` (half fields; a full field is two consecutive halves of
