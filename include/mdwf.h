@@ -352,10 +352,10 @@ typedef struct {
 } mdwf_launch_tune;
 
 /* Autotuner: for each precision (index mdwf_prec), time one Schur operator
- * application (the two fused hop kernels) on scratch fields, choosing in turn
- * the traversal tile (z-blocks and compact 4D tiles), the link mode, then
- * non-temporal stores and workgroup numbering, and keep the fastest in the
- * context; for FP32 and FP16 it then times one bare hop with the lane-per-site
+ * application (the two fused hop kernels) on scratch fields: the installed
+ * and the default shape, then in turn the traversal tile (z-blocks, spatial
+ * columns and compact 4D tiles), the link mode, non-temporal stores and
+ * workgroup numbering, and keep the fastest in the context; for FP32 and FP16 it then times one bare hop with the lane-per-site
  * kernel and with plane_bt 4, 8, 16 (those dividing T) and keeps a plane run
  * that is at least 2 % faster.  out[3] (may be NULL) receives the chosen
  * shapes.  Needs the action and gauge field; allocates scratch device memory
@@ -397,8 +397,9 @@ mdwf_status mdwf_op_model(const mdwf_ctx *ctx, mdwf_op op, mdwf_prec prec, doubl
  * (layout of mdwf_load_gauge), flowed in place; all directions periodic (the
  * fermion boundary condition plays no part).  plaq (may be NULL) receives
  * the average plaquette before and after.  The links must be SU(3) to
- * rounding (unitary, det 1): the staple links enter through their first two
- * rows, the third being the conjugated cross product of those.  A field
+ * rounding (unitary, det 1): the staple links and the staples enter through
+ * their first two rows, the third being the conjugated cross product of those
+ * (links that are off by some d move the result by a few d).  A field
  * with an entry of U U^+ - 1 or of det U - 1 beyond 1e-10 (or a NaN) is
  * refused with ERR_ARG before anything is written.  Extents >= 2; ERR_ARG
  * on eps <= 0 or nsteps < 0.  Synchronous; allocates one link field and

@@ -16,8 +16,11 @@ namespace mdwf {
 // Waves per SIMD the hop kernels are compiled for.  FP16 with staged links: five
 // (96 VGPRs, no spills); left free, the scheduler takes 130 registers for
 // kernels A / A^+ and they run 20 % slower, at six kernel B of S spills.  The
-// other link modes of FP16 spill at five where B is applied before the hop
-// (D5 at L5 = 5: 81 us for 53).  FP32 and FP64 take what their loads in
+// other link modes of FP16 are left free: held to five they spill where B is
+// applied before the hop (D5 at L5 = 5: 81 us for 53), and of the others kernels
+// A, A^+ and B of K5^-1 S take 76 to 78 registers (six waves) by themselves,
+// kernel B of S B^-1 96 (five; held to six it spills 64 bytes and S B^-1 takes
+// 18 to 30 % longer at L5 = 4 to 7).  FP32 and FP64 take what their loads in
 // flight need: held to four and three waves they spill and run 18 % and 7 %
 // slower.
 template <Prec P, int LM> constexpr int hop_waves_per_eu() { return (P == P16 && LM == 1) ? 5 : 1; }

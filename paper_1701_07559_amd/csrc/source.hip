@@ -6,7 +6,8 @@
 //   start from such sources, Sec. V): N explicit steps of
 //       psi <- psi + sigma^2/(4N) Delta psi,
 //       (Delta psi)(x) = sum_{i = x,y,z} U_i(x) psi(x+i) + U_i(x-i)^+ psi(x-i) - 2 psi(x),
-//   one launch per step, a thread per site and vector.
+//   one launch per step, a lane per site, vector and spin; up to 16 vectors
+//   one wavefront holds a site's.
 // * The 5D right-hand side of a 4D source for the Moebius operator
 //   D5 = D_W (b5 + c5 C) + 1 - C:  b = (1 - c5 D_W) Pbar eta with
 //   (Pbar eta)_{L5-1} = P- eta, (Pbar eta)_0 = P+ eta, whose solution's wall
