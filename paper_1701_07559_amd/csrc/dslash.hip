@@ -20,22 +20,21 @@ namespace mdwf {
 // applied before the hop (D5 at L5 = 5: 81 us for 53), and of the others kernels
 // A, A^+ and B of K5^-1 S take 76 to 78 registers (six waves) by themselves,
 // kernel B of S B^-1 96 (five; held to six it spills 64 bytes and S B^-1 takes
-// 18 to 30 % longer at L5 = 4 to 7).  FP32 and FP64 take what their loads in
-// flight need: held to four and three waves they spill and run 18 % and 7 %
-// slower.
+// 18 to 30 % longer at L5 = 4 to 7).  FP32 takes what its loads in flight need:
+// held to four waves it spills and runs 18 % slower.
 template <Prec P, int LM> constexpr int hop_waves_per_eu() { return (P == P16 && LM == 1) ? 5 : 1; }
-// FP64 kernels with a fifth-dimension operator and no staged links are scheduled
-// for two: at the three that 158 registers allow, fewer loads are in flight and
-// S B^-1 at 24^3 x 32 takes 5 to 7 % longer (L5 = 4 to 7)
+// FP64 kernels are scheduled for two: at the three that their 146 to 168 registers
+// would allow, fewer loads are in flight.  24^3 x 64, L5 = 8, staged links: bare
+// hop 564 -> 480 us, S^+ 1146 -> 1072, S B^-1 1144 -> 1069, S 1170 -> 1147;
+// 24^3 x 32, L5 = 4, links by every lane: bare hop 190 -> 169, D5 474 -> 380, S B^-1
+// 387 -> 361.
+template <Prec P> constexpr int hop_waves_at_most() { return P == P64 ? 2 : 8; }
 template <int K> constexpr bool hop_five() {
     return HopTraits<K>::epi == 1 || HopTraits<K>::epi == 2 || HopTraits<K>::cen >= 4;
 }
-template <Prec P, int K, int LM> constexpr int hop_waves_at_most() {
-    return (P == P64 && LM == 0 && hop_five<K>()) ? 2 : 8;
-}
 
 template <Prec P, int K, int LM>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop_waves_per_eu<P, LM>(), hop_waves_at_most<P, K, LM>()))) k_hop(const Geo g, const HopDev a) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop_waves_per_eu<P, LM>(), hop_waves_at_most<P>()))) k_hop(const Geo g, const HopDev a) {
     using R = typename Real<P>::T;
     using TR = HopTraits<K>;
     const int L5 = g.L5;
