@@ -268,17 +268,17 @@ static mdwf_launch_tune environment_tune(const Geo& g) {
 //    but evict each other's neighbours from L2 (FP16, twelve at
 //    24^3 x 32, L5 = 10: 5068 us for 5660 us; six FP64 at 16^3 x 32, 2049 for 2287).
 //    Up to L5 = 5 the links are 1.2 to 1.5 times a right-hand side's field and
-//    nothing stages them: FP64 takes all together (S at L5 = 4, 14^2 x 10 x 26, six:
-//    244 us for 258, bare hop 126 for 151; 22 x 6 x 18 x 60, eleven: 1119 for
-//    1215 and 573 for 692; at L5 = 6 and 7 S is 6 % faster to 27 % slower so,
-//    the bare hop 19 % faster to 5 % slower), FP32 and FP16 two at a time
-//    (24 x 26 x 14 x 24, two FP16: 88 us for 90, bare hop 42 for 46)
+//    nothing stages them: two at a time (24 x 26 x 14 x 24, L5 = 4, two FP16:
+//    88 us for 90, bare hop 42 for 46; FP64 at L5 = 5 between 11 % faster and 4 %
+//    slower), FP64 up to L5 = 4 all together (S, 14 x 8 x 28 x 20, six: 286 us
+//    for 308, two at a time 282; 4 x 28 x 6 x 18, eleven: 115 for 131 and 121).
+//    At L5 = 6 and 7 one after the other is up to 17 % faster, at most 6 % slower
 //  - FP16 results stored past L2, which the next kernel's first reads don't
 //    find there either way (twelve at 24^3 x 64: 7550 us for 7730 us; FP32 and FP64
 //    measure the same)
 static mdwf_launch_tune default_tune(const Geo& g, Prec p, const mdwf_launch_tune& e) {
     mdwf_launch_tune t{{g.Xh, g.Y, (g.Z % 4 == 0) ? 4 : 2, 1}, 1, p == P16, 1, 1, 0.0, 0};
-    if (g.L5 > 0 && g.L5 <= 5) t.rhs_group = p == P64 ? 0 : 2;
+    if (g.L5 > 0 && g.L5 <= 5) t.rhs_group = p == P64 && g.L5 <= 4 ? 0 : 2;
     const bool collide = long(g.Xh) * (g.Y / 2) * g.L5 * 16 == 8192 && long(g.Vh) * 16 % (4L << 20) == 0;
     if (g.Z % 4 == 0 && g.Xh * (g.Y / 2) * (g.Z / 4) >= 192 && !collide) {
         t.tile[1] = g.Y / 2;

@@ -37,7 +37,7 @@ def test_default_tile(M, dims, L5, kind):
     assert all(t["tile"] == want for t in shape(M, dims, L5))
 
 
-@pytest.mark.parametrize("L5,groups", [(4, [0, 2, 2]), (5, [0, 2, 2]), (6, [1, 1, 1]), (8, [1, 1, 1])])
+@pytest.mark.parametrize("L5,groups", [(4, [0, 2, 2]), (5, [2, 2, 2]), (6, [1, 1, 1]), (8, [1, 1, 1])])
 def test_default_rhs_group(M, L5, groups):
     assert [t["rhs_group"] for t in shape(M, (12, 12, 12, 8), L5)] == groups
 

@@ -51,7 +51,7 @@ def program(tmp_path_factory):
 @pytest.mark.parametrize("dims,L5,tile,group", [
     ((32, 32, 32, 64), 8, "16,16,8,2", "1 1 1"), ((20, 20, 20, 40), 10, "10,10,5,2", "1 1 1"),
     ((24, 24, 24, 64), 8, "12,12,6,2", "1 1 1"), ((16, 16, 16, 16), 8, "8,16,4,1", "1 1 1"),
-    ((18, 18, 18, 24), 12, "9,18,2,1", "1 1 1"), ((30, 20, 24, 6), 5, "15,10,6,2", "0 2 2")])
+    ((18, 18, 18, 24), 12, "9,18,2,1", "1 1 1"), ((30, 20, 24, 6), 5, "15,10,6,2", "2 2 2"), ((30, 20, 24, 6), 4, "15,10,6,2", "0 2 2")])
 def test_the_default_is_timed(program, dims, L5, tile, group):
     out = subprocess.run([program] + [str(v) for v in dims + (L5,)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stderr
