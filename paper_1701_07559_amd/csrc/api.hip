@@ -271,7 +271,7 @@ static mdwf_launch_tune environment_tune(const Geo& g) {
 //    nothing stages them: two at a time (24 x 26 x 14 x 24, L5 = 4, two FP16:
 //    88 us for 90, bare hop 42 for 46; FP64 at L5 = 5 between 11 % faster and 4 %
 //    slower), FP64 up to L5 = 4 all together (S, 14 x 8 x 28 x 20, six: 286 us
-//    for 308, two at a time 282; 4 x 28 x 6 x 18, eleven: 115 for 131 and 121).
+//    for 309, two at a time 283; 4 x 28 x 6 x 18, eleven: 115 for 131 and 121).
 //    At L5 = 6 and 7 one after the other is up to 17 % faster, at most 6 % slower
 //  - FP16 results stored past L2, which the next kernel's first reads don't
 //    find there either way (twelve at 24^3 x 64: 7550 us for 7730 us; FP32 and FP64

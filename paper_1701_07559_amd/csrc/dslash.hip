@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(hop
     // five_lanes in the same bytes
     constexpr int kLinkBytes = LM == 1 ? stage_bytes<P>() : 0;
     constexpr bool kFive = hop_five<K>();
-    constexpr int kFiveBytes = kFive ? (five_bytes<R>() + 15) / 16 * 16 : 0;
+    constexpr int kFiveBytes = kFive ? (five_bytes<P, LM != 1>() + 15) / 16 * 16 : 0;
     constexpr int kSmem = kLinkBytes > kFiveBytes ? kLinkBytes : kFiveBytes;
     __shared__ __align__(16) unsigned char smem[kWaves][kSmem > 0 ? kSmem : 16];
     unsigned char* const lw = smem[wave];

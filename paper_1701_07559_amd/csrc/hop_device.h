@@ -558,7 +558,14 @@ __device__ __forceinline__ void dir_term(cx<typename Real<P>::T> acc[12], const 
 // element further apart than the lanes so that the lanes of its recurrence
 // fall into different banks
 constexpr int kFivePitch = 64 + 1;
-template <typename R> constexpr int five_bytes() { return 6 * kFivePitch * int(sizeof(cx<R>)); }
+// C: the recurrence's type; S: the tile's
+template <Prec P, bool TERMS> struct FiveReal {
+    using C = typename std::conditional<P == P16, float, double>::type;
+    using S = typename std::conditional<TERMS, typename Real<P>::T, C>::type;
+};
+template <Prec P, bool TERMS> constexpr int five_bytes() {
+    return 6 * kFivePitch * int(sizeof(cx<typename FiveReal<P, TERMS>::S>));
+}
 
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -583,8 +590,11 @@ __device__ __forceinline__ void wave_sync() {
 // every slice, a rounded z among the causes: in FP32 up to 2.8 times the dense
 // sum's (alternating slices, |z| = 0.53, L5 = 21, m_q = 1).  FP32 fields
 // therefore run it in FP64, whose FMA has the FP32 one's rate, and round the
-// result once: 0.06 to 0.7 times the dense sum's error, for 1 to 3 % of the
-// operator's time.  FP64 fields take coefficients rounded once from extended
+// result once: 0.06 to 0.7 times the dense sum's error.  With staged links the
+// tile is FP64 too, every lane converting its own values (S B^-1 at 24^3 x 64,
+// L5 = 8: 592 us, 615 with an FP32 tile, 606 with the recurrence in FP32);
+// the other link modes, which hold the term sums beside it, keep an FP32 tile
+// (an FP64 one costs their kernel A of S 35 registers and S 13 %).  FP64 fields take coefficients rounded once from extended
 // precision (half the dense sum's error in the median over actions and L5,
 // 2.6 times in the worst case found, both below 1.2e-15); FP16 fields FP32
 // ones, which their storage's rounding hides (error with the dense sums'
@@ -631,19 +641,21 @@ __device__ __forceinline__ void five_lanes(cx<typename Real<P>::T> v[12], cx<typ
         }
         return;
     }
-    using C = typename std::conditional<P == P32, double, R>::type;
+    using C = typename FiveReal<P, TERMS>::C;
+    using S = typename FiveReal<P, TERMS>::S;
     const C A = C(rec.A), B = C(rec.B), z = C(rec.z), w = C(rec.w);
-    auto in = [](cx<R> x) { return cx<C>{C(x.re), C(x.im)}; };
+    cx<S>* const t = reinterpret_cast<cx<S>*>(tile);
+    auto in = [](cx<S> x) { return cx<C>{C(x.re), C(x.im)}; };
     wave_sync();   // the tile's bytes may hold the wave's links until here
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
 #pragma unroll
-        for (int c = 0; c < 6; ++c) tile[c * kFivePitch + lane] = v[6 * half + c];
+        for (int c = 0; c < 6; ++c) t[c * kFivePitch + lane] = {S(v[6 * half + c].re), S(v[6 * half + c].im)};
         wave_sync();
         const bool up = (half == 0) != ADJ;   // slice s reads s - 1
         for (int e = lane; e < 6 * spw; e += 64) {
             const int i = int((uint32_t(e) * 10923u) >> 16), c = e - 6 * i;   // e / 6 (e < 384)
-            cx<R>* col = tile + c * kFivePitch + i * L5 + (up ? 0 : L5 - 1);
+            cx<S>* col = t + c * kFivePitch + i * L5 + (up ? 0 : L5 - 1);
             const int st = up ? 1 : -1;
             cx<C> T = in(col[0]);
 #pragma unroll 4
@@ -652,13 +664,13 @@ __device__ __forceinline__ void five_lanes(cx<typename Real<P>::T> v[12], cx<typ
 #pragma unroll 4
             for (int k = 0; k < L5; ++k) {
                 const cx<C> x = in(col[k * st]), o = axpy(A, x, B * f);
-                col[k * st] = {R(o.re), R(o.im)};
+                col[k * st] = {S(o.re), S(o.im)};
                 f = axpy(z, f, x);
             }
         }
         wave_sync();
 #pragma unroll
-        for (int c = 0; c < 6; ++c) v[6 * half + c] = tile[c * kFivePitch + lane];
+        for (int c = 0; c < 6; ++c) v[6 * half + c] = {R(t[c * kFivePitch + lane].re), R(t[c * kFivePitch + lane].im)};
         if (half == 0) wave_sync();
     }
 }
