@@ -331,8 +331,8 @@ typedef struct {
     int nt_store;    /* 1: hop outputs written with non-temporal stores               */
     int link_mode;   /* links: 0 loaded by every lane, 1 staged in LDS (L5 >= 8; in
                         FP32 on lattices of more than 350 workgroups a
-                        right-hand side for the bare hops, 2500 for D5 and
-                        the Schur right-hand side, 4000 for the Schur forms),
+                        right-hand side for the bare hops, 4000 for S and
+                        S^+, 2500 for the other operators),
                         2 one 16-byte part per lane, gathered by lane exchange
                         (FP32 / FP16, L5 >= 4 / 2), 3 FP16 SU(3) products on
                         the matrix cores (4x4x4 blocks of four slices of one

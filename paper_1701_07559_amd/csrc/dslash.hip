@@ -305,13 +305,15 @@ int hop_blocks_per_rhs(const Geo& g) {
 //   bare hops       128 workgroups: 1.12, 216: 1.09, 432: 1.01, 1080: 0.96, 3000: 0.85
 //                   (four right-hand sides: 1.01, 0.96, 0.93, 0.88, 0.91)
 //   D5 and adjoint  1080: 1.02 and 1.18, 2304: 1.01 and 1.07, 2560: 0.97 and 1.00, 3000: 0.96
-//   S, S B^-1       1080: 1.13 and 1.22, 2304: 1.09 and 1.17, 3840: 1.03 and 1.10,
-//                   4096: 0.96 to 1.04 and 0.95 to 1.09, 6048: 0.98 and 0.96
+//   S B^-1          432: 1.05, 1792: 1.01, 2304: 1.00, 2560: 0.99, 3000: 0.96, 3600: 0.92
+//   S, S^+          1080: 1.15 and 1.12, 2304: 1.11, 3000: 1.04, 3755: 1.04, 4096: 1.04 and
+//                   1.00, 4320: 0.98 and 0.96 (kernels A, B and B^+ of it; A^+ is S B^-1's)
 // (FP64, with three times the link loads to save, is staged everywhere: below 500
 // workgroups S is up to 3 % slower and S B^-1 4 to 9 % faster.  FP16 too: 0 to 6 %
 // slower below 4000, faster above.)
 template <int K> constexpr int stage_blocks_f32() {
-    return K == HOP_BARE || K == HOP_BARE_DAG ? 350 : K == HOP_D5 || K == HOP_D5_DAG || K == HOP_PREP ? 2500 : 4000;
+    if (K == HOP_BARE || K == HOP_BARE_DAG) return 350;
+    return K == HOP_SCHUR_A || K == HOP_SCHUR_B || K == HOP_SCHUR_B_DAG ? 4000 : 2500;
 }
 
 template <Prec P, int K>
