@@ -594,15 +594,15 @@ __device__ __forceinline__ void wave_sync() {
 // tile is FP64 too, every lane converting its own values (S B^-1 at 24^3 x 64,
 // L5 = 8: 592 us, 615 with an FP32 tile, 606 with the recurrence in FP32);
 // the other link modes, which hold the term sums beside it, keep an FP32 tile
-// (an FP64 one costs their kernel A of S 35 registers and S 13 %).  FP64 fields take coefficients rounded once from extended
-// precision (half the dense sum's error in the median over actions and L5,
-// 2.6 times in the worst case found, both below 1.2e-15); FP16 fields FP32
-// ones, which their storage's rounding hides (error with the dense sums'
-// coefficients to 3e-5 of it).
+// (an FP64 one costs their kernel A of S 35 registers and S 13 %).  FP64 fields
+// take coefficients rounded once from extended precision (half the dense sum's
+// error in the median over actions and L5, 2.6 times in the worst case found,
+// both below 1.2e-15); FP16 fields FP32 ones, which their storage's rounding
+// hides (error with the dense sums' coefficients to 3e-5 of it).
 // Up to L5 = 6 the chain along the slices takes longer than the L5 - 1 terms
 // themselves: each lane sums its own slice's, with coefficients formed in FP64
-// and rounded once, those across the wall times -m_q.  (Of the operators with these sums the
-// recurrence cost FP64 S B^-1 7 % at L5 = 6 and nothing at L5 = 7.)
+// and rounded once, those across the wall times -m_q.  (Of the operators with
+// these sums the recurrence cost FP64 S B^-1 7 % at L5 = 6 and nothing at L5 = 7.)
 template <Prec P, bool ADJ, bool TERMS>
 __device__ __forceinline__ void five_lanes(cx<typename Real<P>::T> v[12], cx<typename Real<P>::T>* tile,
                                            const FiveRec& rec, double mq, int lane, int L5, int spw) {
