@@ -236,13 +236,13 @@ def hop_launch_bytes(inner, Vh, nr):
 # What the counters show limits the hop kernels below the HBM roofline
 # (rocprofv3 summaries under profiles/).
 LIMITER = {
-    "f16": "co-limited: texture addresser 94-97% busy on 56-61 load instructions per wave "
-           "(profiles/hop_ta_busy_24c64_L8_12rhs.md) and VALU 89% busy in kernels A / A_dag, 73-76% in B / B_dag "
-           "(profiles/hop_valu_busy_24c64_L8.md), moving 5.9-6.7 TB/s beyond L2, 2.2x the algorithmic bytes "
+    "f16": "co-limited: texture addresser 95-96% busy on 35-39 load instructions per wave "
+           "(profiles/hop_ta_busy_24c64_L8_12rhs.md) and VALU 73-77% busy "
+           "(profiles/hop_valu_busy_24c64_L8.md), moving 5.3 TB/s beyond L2, 1.7x the algorithmic bytes "
            "(profiles/schur_rp_f16_24c64_L8_12rhs_counters.md)",
-    "f32": "re-reads of the input field beyond L2 (2.26x) at a rate near the streaming limit "
-           "(profiles/hop_f32_plane_24c64_L8_counters.md)",
-    "f64": "re-reads of the input field beyond L2 (1.75-2.5x) at 5.3-6.6 TB/s "
+    "f32": "re-reads of the input field beyond L2 (1.6-2.1x) at 4.7-5.8 TB/s, texture addresser 77-93% busy "
+           "(profiles/hop_f32_24c64_L8_counters.md)",
+    "f64": "re-reads of the input field beyond L2 (1.75-2.1x) at 5.1-6.7 TB/s "
            "(profiles/hop_f64_24c64_L8_counters.md)",
 }
 
@@ -252,8 +252,9 @@ LIMITER = {
 # VALU instructions that execute them, without packed FP32: the eight SU(3)
 # products (8 x 132 flops) as v_dot2_f32_f16 at 4 flops per lane, the eight
 # projections (8 x 12) as packed-half adds at 2, the sum over directions
-# (168) as FP32 adds at 1, the dense fifth-dimension polynomial (48 L5) and
-# B's combination (48) as FP32 FMAs at 2.  One VALU instruction per lane and
+# (168) as FP32 adds at 1, the dense fifth-dimension polynomial (48 L5; the
+# kernels' recurrences take 192 whatever L5) and B's combination (48) as FP32
+# FMAs at 2.  One VALU instruction per lane and
 # cycle on 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz then gives the peak flop
 # rate of this instruction mix.
 VALU_LANE_RATE = 256 * 4 * 16 * 2.4e9
@@ -519,13 +520,20 @@ def pmc_summary(args):
     print(text)
 
 
-# Gradient flow model per link and Runge-Kutta stage: 26 products of 3x3
+# Gradient flow model per link and Runge-Kutta stage in full matrices: 26 products of 3x3
 # complex matrices (12 for the six staples, one for the link times their sum,
 # 12 for the degree-12 Taylor exponential, one for the update; 216 flops each)
 # and, in FP64, the input link and the output link read / written once (144 B
 # each) and the exponent accumulator, eight reals (64 B), read and written
 # (written only by the first stage).
 FLOW_FLOPS_PER_LINK = 26 * 216
+# What the stage kernel executes of it: two rows of each product of the six
+# staples (144 flops a product) with third rows as conjugated cross products
+# (14 an entry), three lower staples of 460 and three upper ones of 432, the
+# link times their sum and the exponential times the link (216 each), the
+# traceless part and the accumulator (30) and the exponential by its three
+# complex coefficients (367)
+FLOW_STAGE_FLOPS_PER_LINK = 3 * (460 + 432) + 2 * 216 + 30 + 367
 FLOW_BYTES_PER_LINK = ((144 + 144 + 64) + 2 * (144 + 144 + 64 + 64)) / 3.0
 
 
@@ -569,7 +577,7 @@ def flow_main(args):
     ms = 1e3 * float(np.mean(times))
     stage_us = float(np.mean(kern))
     bytes_step = FLOW_BYTES_PER_LINK * nlinks * 3 * nsteps
-    flops_stage = FLOW_FLOPS_PER_LINK * nlinks
+    flops_stage = FLOW_STAGE_FLOPS_PER_LINK * nlinks
     value = bytes_step / (ms * 1e-3) / 1e9
     achieved = flops_stage / (stage_us * 1e-6) / 1e12
     cpu = None
@@ -610,7 +618,8 @@ def flow_main(args):
         "roofline": {"bound": "alu", "kernel": "k_flow_stage (one Runge-Kutta stage, FP64)",
                      "achieved": round(achieved, 2), "peak": 78.6, "unit": "TFLOP/s",
                      "frac": round(achieved / 78.6, 4), "traffic": None,
-                     "model": "26 complex 3x3 products per link and stage (216 flops each)"},
+                     "model": "%d flops per link and stage, as the kernel executes them (26 complex 3x3 products "
+                              "of 216 in full matrices)" % FLOW_STAGE_FLOPS_PER_LINK},
         "cpu_baseline": cpu,
     }
     print(json.dumps(out), flush=True)
