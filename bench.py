@@ -238,7 +238,7 @@ def hop_launch_bytes(inner, Vh, nr):
 LIMITER = {
     "f16": "co-limited: texture addresser 95-96% busy on 35-39 load instructions per wave "
            "(profiles/hop_ta_busy_24c64_L8_12rhs.md) and VALU 73-77% busy "
-           "(profiles/hop_valu_busy_24c64_L8.md), moving 5.3 TB/s beyond L2, 1.7x the algorithmic bytes "
+           "(profiles/hop_valu_busy_24c64_L8.md), moving 5.3 TB/s beyond L2, 1.75x the algorithmic bytes "
            "(profiles/schur_rp_f16_24c64_L8_12rhs_counters.md)",
     "f32": "re-reads of the input field beyond L2 (1.6-2.1x) at 4.7-5.8 TB/s, texture addresser 77-93% busy "
            "(profiles/hop_f32_24c64_L8_counters.md)",
@@ -247,7 +247,7 @@ LIMITER = {
 }
 
 # Vector-ALU roofline of the FP16-storage hop kernels, which the counters show
-# issue-bound.  Per 5D site and RHS the model flops of kernel A / B of the
+# bound by addresser and issue.  Per 5D site and RHS the model flops of kernel A / B of the
 # CG operator are 1320 + 48 L5 (+ 48 for B's combination).  The fewest gfx950
 # VALU instructions that execute them, without packed FP32: the eight SU(3)
 # products (8 x 132 flops) as v_dot2_f32_f16 at 4 flops per lane, the eight
@@ -291,8 +291,8 @@ def roofline(info, inner, Vh, form):
                 for n, u, b in zip(names, us, by)}
     hbm = dict(achieved=round(ach, 1), peak=HBM_PEAK_GBS, unit="GB/s", frac=round(ach / HBM_PEAK_GBS, 4))
     if inner == "f16" and form == "rp":
-        # issue-bound (VALU busy 73-90 %): priced against the vector ALUs,
-        # the HBM fraction kept beside it
+        # addresser and issue bound (VALU busy 73-77 %): priced against the
+        # vector ALUs, the HBM fraction kept beside it
         fl = hop_launch_flops(Vh, nr, form)
         tf = (fl[0] + fl[1]) / ((us[0] + us[1]) * 1e-6) / 1e12
         pk = alu_peak_tflops(L5)
@@ -300,7 +300,9 @@ def roofline(info, inner, Vh, form):
                     frac=round(tf / pk, 4),
                     peak_derivation="model flops of kernels A+B over the fewest VALU instructions that execute "
                                     "them (SU(3) products as v_dot2_f32_f16, FP32 sums, packed-half projections), "
-                                    "one VALU instruction per lane and cycle, 256 CUs x 64 lanes x 2.4 GHz",
+                                    "one VALU instruction per lane and cycle, 256 CUs x 64 lanes x 2.4 GHz; the model "
+                                    "holds the dense fifth-dimension sum, which the kernels run as a recurrence "
+                                    "(192 flops for 48 L5)",
                     frac_of_fp32_vector_peak=round(tf / 157.3, 4),
                     traffic=None, hbm=hbm, limiter=LIMITER.get(inner), launches=launches)
     return dict(bound="hbm", kernel=kernel, traffic=None, limiter=LIMITER.get(inner), launches=launches, **hbm)
